@@ -1,6 +1,7 @@
 """Build liblbem.so (HIP for gfx950) in-tree: paper_1108_2651_amd/_build/."""
 from __future__ import annotations
 
+import concurrent.futures as cf
 import os
 import subprocess
 import sys
@@ -9,13 +10,15 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(OUT_DIR, "liblbem.so")
-SOURCES = [os.path.join(CSRC, "lbem.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("kernels.h", "lattice.h")] + [
+# (source, extra flags) of each translation unit, compiled in parallel
+UNITS = [("lbem.hip", [])] + [("impl.hip", [f"-DLBEM_UNIT={k}"]) for k in range(5)]
+SOURCES = [os.path.join(CSRC, f) for f in ("lbem.hip", "impl.hip")]
+HEADERS = [os.path.join(CSRC, f) for f in ("impl.h", "kernels.h", "lattice.h")] + [
     os.path.join(os.path.dirname(HERE), "include", "lbem.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
+    "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
     # keep the compiler from forming packed FP32 (v_pk_*_f32) instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # no implicit a*b+c -> fma contraction: every kernel then rounds the shared
@@ -28,12 +31,25 @@ FLAGS = [
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC] + FLAGS + SOURCES + ["-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    os.replace(tmp, LIB)
+    tag = ".tmp%d" % os.getpid()
+    objs = [os.path.join(OUT_DIR, f"unit{k}{tag}.o") for k in range(len(UNITS))]
+
+    def compile_unit(k):
+        src, extra = UNITS[k]
+        cmd = [HIPCC, "-c"] + FLAGS + extra + [os.path.join(CSRC, src), "-o", objs[k]]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+
+    try:
+        with cf.ThreadPoolExecutor(max_workers=min(len(UNITS), os.cpu_count() or 1)) as pool:
+            list(pool.map(compile_unit, range(len(UNITS))))
+        subprocess.run([HIPCC, "-shared", "--offload-arch=gfx950", "-fPIC"] + objs + ["-o", LIB + tag], check=True)
+        os.replace(LIB + tag, LIB)
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.remove(o)
     return LIB
 
 

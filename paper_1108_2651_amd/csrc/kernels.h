@@ -2604,7 +2604,7 @@ __global__ __launch_bounds__(NT) void k_divb(const double* __restrict__ B, const
     if (threadIdx.x == 0) partials[blockIdx.x * 4 + 2] = r;
 }
 
-__global__ __launch_bounds__(NT) void k_reduce_partials(const double* __restrict__ partials, int nb, double* out)
+static __global__ __launch_bounds__(NT) void k_reduce_partials(const double* __restrict__ partials, int nb, double* out)
 {
     __shared__ double sh[4];
     for (int k = 0; k < 4; ++k) {
