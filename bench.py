@@ -85,7 +85,8 @@ def kernel_source_hash() -> str:
     instantiation is checked separately, by the kernel name recorded with the
     counters."""
     h = hashlib.sha256()
-    for f in ("paper_1108_2651_amd/csrc/kernels.h", "paper_1108_2651_amd/csrc/lattice.h", "paper_1108_2651_amd/csrc/impl.h",
+    for f in ("paper_1108_2651_amd/csrc/kernels.h", "paper_1108_2651_amd/csrc/march2d.h",
+              "paper_1108_2651_amd/csrc/lattice.h", "paper_1108_2651_amd/csrc/impl.h",
               "paper_1108_2651_amd/csrc/impl.hip", "paper_1108_2651_amd/csrc/lbem.hip"):
         h.update(_code_only(open(os.path.join(ROOT, f), encoding="utf-8").read()).encode())
     h.update(open(os.path.join(ROOT, "paper_1108_2651_amd/build.py"), "rb").read())

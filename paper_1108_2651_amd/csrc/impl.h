@@ -14,6 +14,7 @@
 
 #include "../../include/lbem.h"
 #include "kernels.h"
+#include "march2d.h"
 
 using namespace lbem;
 
@@ -144,9 +145,16 @@ struct lbem_s {
     // tiling of the step kernels
     Geo geo;
     int vec;
-    // temporal blocking (fuse_ns steps per launch; 1 = off): 2D tiles 64 x fuse_ty,
-    // 3D column tiles f3_tx x f3_ty marching over chunks of f3_lz planes
-    int fuse_ns, fuse_ty, fuse_nt;
+    // temporal blocking (fuse_ns steps per launch; 1 = off): 2D wave strips of
+    // mcpl cells per lane, mwpb waves per block; 3D column tiles f3_tx x f3_ty
+    // marching over chunks of f3_lz planes
+    int fuse_ns;
+    MarchGeo mgeo;
+    int mcpl, mwpb;
+    int* msrc_idx;
+    void* msrc_val;
+    unsigned msrc_mask[8];
+    int64_t nmsrc;       // source segments of the strips
     int f3_tx, f3_ty, f3_lz;
     Geo fgeo;
     int* fsrc_off;
@@ -256,8 +264,9 @@ static void stage_free(Staging& st, hipStream_t s)
 struct Impl {
     virtual ~Impl() {}
     virtual hipError_t step(lbem_s* h, double amp) = 0;
-    // advance h->fuse_ns steps in one launch (only when fused_ok and pull-pending)
-    virtual hipError_t step_fused(lbem_s* h, const double* amp) { return hipErrorInvalidValue; }
+    // advance ns steps in one launch (2D: 2..fuse_ns, 3D: fuse_ns; only when
+    // fused_ok and pull-pending)
+    virtual hipError_t step_fused(lbem_s* h, const double* amp, int ns) { return hipErrorInvalidValue; }
     virtual hipError_t fields(lbem_s* h, double* E, double* B, double* partials) = 0;
     virtual hipError_t init(lbem_s* h, const double* dE, const double* dB) = 0;
     virtual hipError_t medium(lbem_s* h, const double* deps, const double* dmu, int* dflag) = 0;
@@ -316,71 +325,54 @@ static hipError_t launch_fields(lbem_s* h, const R& rd, double* E, double* B, do
     return hipGetLastError();
 }
 
-// fused 2D launches: (steps per launch, tile rows) pairs that are instantiated
-// The paper's tau = 1/2 gets its own instantiation: the reflection collision
-// folds at compile time (measured 2 % faster at 2048^2, 12 % at 8192^2 with
-// four steps per launch); other tau take the general one.
-template <typename T, int NS, int TY, bool MU, bool O32, bool NTS, int NTB>
-static void launch_fused2d(lbem_s* h, const T* src, T* dst, const FusedSrc<T>& fs, const AmpPack<T, NS>& a)
+// 2D multi-step launches (k_march2d).  The paper's tau = 1/2 gets its own
+// instantiation: the reflection collision folds at compile time.
+template <class IO, int NS, int CPL, bool MU, bool TH>
+static void launch_march(lbem_s* h, const IO& io, const double* amp)
 {
-    const T om = (T)(1.0 / h->cfg.tau);
-    if (h->cfg.tau == 0.5)
-        hipLaunchKernelGGL((k_step_fused2d<T, NS, TY, MU, O32, NTS, true, NTB>), dim3(h->fgeo.nblocks), dim3(NTB), 0,
-                           h->stream, src, dst, (const T*)h->cl2, (const T*)h->dlnmu, h->fgeo, fs, a, om, 1);
-    else
-        hipLaunchKernelGGL((k_step_fused2d<T, NS, TY, MU, O32, NTS, false, NTB>), dim3(h->fgeo.nblocks), dim3(NTB), 0,
-                           h->stream, src, dst, (const T*)h->cl2, (const T*)h->dlnmu, h->fgeo, fs, a, om, 0);
-}
-
-template <typename T, int NS, int TY, bool MU, int NTB>
-static hipError_t go_fused_ntm(lbem_s* h, const T* src, T* dst, const double* amp)
-{
-    FusedSrc<T> fs;
-    fs.off = h->nfsrc ? h->fsrc_off : nullptr;
-    fs.ent = h->fsrc_ent;
-    fs.val = (const T*)h->fsrc_val;
+    typedef typename IO::T T;
+    MarchSrc<T> ms;
+    ms.idx = h->msrc_idx;
+    ms.val = (const T*)h->msrc_val;
+    for (int k = 0; k < 8; ++k) ms.mask[k] = h->nmsrc ? h->msrc_mask[k] : 0u;
     AmpPack<T, NS> a;
     for (int j = 0; j < NS; ++j) a.a[j] = (T)(amp ? amp[j] : 0.0);
-    // 32-bit element offsets while one population plane fits 2^32 bytes;
-    // streaming stores beyond the last-level cache (2-3 % there)
-    if ((uint64_t)h->n * sizeof(T) <= (1ull << 32) && h->nts)
-        launch_fused2d<T, NS, TY, MU, true, true, NTB>(h, src, dst, fs, a);
-    else if ((uint64_t)h->n * sizeof(T) <= (1ull << 32))
-        launch_fused2d<T, NS, TY, MU, true, false, NTB>(h, src, dst, fs, a);
-    else
-        launch_fused2d<T, NS, TY, MU, false, false, NTB>(h, src, dst, fs, a);
+    hipLaunchKernelGGL((k_march2d<IO, NS, CPL, MU, TH>), dim3(h->mgeo.nblocks), dim3(64 * h->mwpb), 0, h->stream, io,
+                       (const T*)h->cl2, (const T*)h->dlnmu, h->mgeo, ms, a, (T)(1.0 / h->cfg.tau),
+                       (int)(h->cfg.tau == 0.5));
+}
+
+template <class IO, int NS, int CPL, bool MU>
+static void launch_march_th(lbem_s* h, const IO& io, const double* amp)
+{
+    if (h->cfg.tau == 0.5) launch_march<IO, NS, CPL, MU, true>(h, io, amp);
+    else launch_march<IO, NS, CPL, MU, false>(h, io, amp);
+}
+
+template <class IO, int CPL>
+static hipError_t go_march(lbem_s* h, const IO& io, const double* amp, int ns)
+{
+    if (h->mu_set) {
+        if (ns == 4) launch_march_th<IO, 4, CPL, true>(h, io, amp);
+        else if (ns == 3) launch_march_th<IO, 3, CPL, true>(h, io, amp);
+        else if (ns == 2) launch_march_th<IO, 2, CPL, true>(h, io, amp);
+        else return hipErrorInvalidValue;
+    } else {
+        if (ns == 4) launch_march_th<IO, 4, CPL, false>(h, io, amp);
+        else if (ns == 3) launch_march_th<IO, 3, CPL, false>(h, io, amp);
+        else if (ns == 2) launch_march_th<IO, 2, CPL, false>(h, io, amp);
+        else return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
-template <typename T, int NS, int TY, int NTB = NT>
-static hipError_t go_fused_nt(lbem_s* h, const T* src, T* dst, const double* amp)
-{
-    if (h->mu_set) return go_fused_ntm<T, NS, TY, true, NTB>(h, src, dst, amp);
-    return go_fused_ntm<T, NS, TY, false, NTB>(h, src, dst, amp);
-}
-
 template <typename T>
-static hipError_t go_fused(lbem_s* h, const T* src, T* dst, const double* amp)
+static hipError_t go_fused(lbem_s* h, const T* src, T* dst, const double* amp, int ns)
 {
-    const int ns = h->fuse_ns, ty = h->fuse_ty;
     if constexpr (sizeof(T) == 4) {
-        if (h->fuse_nt == 512) {
-            if (ns == 2 && ty == 16) return go_fused_nt<T, 2, 16, 512>(h, src, dst, amp);
-            if (ns == 2 && ty == 32) return go_fused_nt<T, 2, 32, 512>(h, src, dst, amp);
-            if (ns == 4 && ty == 16) return go_fused_nt<T, 4, 16, 512>(h, src, dst, amp);
-        }
-        if (ns == 2 && ty == 16) return go_fused_nt<T, 2, 16>(h, src, dst, amp);
-        if (ns == 2 && ty == 8) return go_fused_nt<T, 2, 8>(h, src, dst, amp);
-        if (ns == 2 && ty == 4) return go_fused_nt<T, 2, 4>(h, src, dst, amp);
-        if (ns == 3 && ty == 16) return go_fused_nt<T, 3, 16>(h, src, dst, amp);
-        if (ns == 4 && ty == 16) return go_fused_nt<T, 4, 16>(h, src, dst, amp);
-        if (ns == 4 && ty == 8) return go_fused_nt<T, 4, 8>(h, src, dst, amp);
-    } else {
-        if (ns == 2 && ty == 8) return go_fused_nt<T, 2, 8>(h, src, dst, amp);
-        if (ns == 2 && ty == 4) return go_fused_nt<T, 2, 4>(h, src, dst, amp);
-        if (ns == 3 && ty == 8) return go_fused_nt<T, 3, 8>(h, src, dst, amp);
+        if (h->mcpl == 2) return go_march<MarchPlain<T, 2>, 2>(h, MarchPlain<T, 2>{src, dst, h->n}, amp, ns);
     }
-    return hipErrorInvalidValue;
+    return go_march<MarchPlain<T, 1>, 1>(h, MarchPlain<T, 1>{src, dst, h->n}, amp, ns);
 }
 
 template <typename T, int TX, int TY, bool MU, bool NTS>
@@ -511,7 +503,7 @@ struct PlainImpl : Impl {
         h->layout = LAYOUT_PULL_PENDING;
         return e;
     }
-    hipError_t step_fused(lbem_s* h, const double* amp) override
+    hipError_t step_fused(lbem_s* h, const double* amp, int ns) override
     {
         if constexpr (!std::is_same<S, T>::value) {
             return hipErrorInvalidValue;   // the multi-step kernels keep FP64/FP32 storage
@@ -519,7 +511,7 @@ struct PlainImpl : Impl {
             const T* a = (const T*)h->pop[h->cur];
             T* b = (T*)h->pop[1 - h->cur];
             hipError_t e;
-            if constexpr (D == 2) e = go_fused<T>(h, a, b, amp);
+            if constexpr (D == 2) e = go_fused<T>(h, a, b, amp, ns);
             else e = go_fused3<T>(h, a, b, amp);
             h->cur = 1 - h->cur;
             return e;
@@ -684,7 +676,7 @@ struct DevImpl : Impl {
         h->layout = LAYOUT_PULL_PENDING;
         return e;
     }
-    hipError_t step_fused(lbem_s* h, const double* amp) override
+    hipError_t step_fused(lbem_s* h, const double* amp, int ns) override
     {
         if constexpr (D == 3) {
             FusedSrc<float> fs;

@@ -669,33 +669,8 @@ __global__ __launch_bounds__(NT) void k_step_xrow(const S* src, S* dst, const T*
     }
 }
 
-// ---------------------------------------------------------------------------
-// 2D temporal blocking: NS time steps per launch (plain formats, pull)
-// ---------------------------------------------------------------------------
-// A block owns an output tile of TXF x TY cells.  All work happens in one LDS
-// frame: the tile grown by H = NS-1 cells on every side.  Step 1 pulls the
-// stored populations from HBM for the whole frame and collides; steps 2..NS
-// pull from the previous LDS layer, each on a region one cell smaller, the
-// last one on the tile itself, which is written back.  State bytes therefore
-// cross HBM once per NS steps; every cell update runs the same collide() code
-// as the single-step kernel, so NS fused steps equal NS single steps bit for
-// bit.  Periodic wrap is applied to the frame's global coordinates.
-constexpr int TXF = 64;
-
-// Element idx of an array whose byte size fits 32 bits: the offset is formed
-// in 32-bit arithmetic, so the load or store takes the scalar-base plus
-// 32-bit vector-offset form and needs no 64-bit address arithmetic.
-template <typename T>
-__device__ __forceinline__ T& at32(T* base, unsigned idx)
-{
-    return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + idx * (unsigned)sizeof(T));
-}
-template <typename T>
-__device__ __forceinline__ const T& at32(const T* base, unsigned idx)
-{
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + idx * (unsigned)sizeof(T));
-}
-
+// Sparse current source of the 3D multi-step tilings: per block a range
+// [off[b], off[b+1]) of entries.
 template <typename T>
 struct FusedSrc {
     const int* off;      // per tile range into ent/val (nullptr: no source)
@@ -707,161 +682,6 @@ template <typename T, int NS>
 struct AmpPack {
     T a[NS];             // source amplitude of each fused step
 };
-
-// O32: every population plane fits 2^32 bytes (32-bit element offsets)
-// NTS: streaming stores of the state (lattices beyond the last-level cache).
-// TH: tau = 1/2 known when compiling (the reflection collision, whatever
-// tau_half says), else tau_half chooses at run time.
-template <typename T, int NS, int TY, bool MU, bool O32, bool NTS, bool TH, int NTB = NT>
-__global__ __launch_bounds__(NTB) void k_step_fused2d(const T* src, T* dst, const T* __restrict__ cl2a,
-                                                    const T* __restrict__ dlnmu, const Geo g,
-                                                    const FusedSrc<T> fs, const AmpPack<T, NS> amps,
-                                                    const T omega, const int tau_half)
-{
-    constexpr int H = NS - 1;
-    constexpr int W = TXF + 2 * H;          // frame width
-    constexpr int FH = TY + 2 * H;          // frame height
-    constexpr int FC = W * FH;
-    constexpr int NB = NS > 2 ? 2 : 1;      // LDS population layers
-    constexpr int Q = 5;
-    __shared__ T lp[NB][Q][FC];
-    __shared__ T lc[FC];
-    __shared__ T ls[FC];
-    __shared__ T ldl[MU ? 2 : 1][MU ? FC : 1];   // grad ln mu of the frame
-
-    const int b = remap_block(blockIdx.x, g.nblocks, g.xcd);
-    const int tx = b % g.tiles_x, ty = b / g.tiles_x;
-    const int x0 = tx * TXF - H, y0 = ty * TY - H;     // global coords of frame (0,0)
-
-    // source coefficients of the frame (tiles that own none skip this)
-    bool has_src = false;
-    if (fs.off) {
-        const int s0 = fs.off[b], s1 = fs.off[b + 1];
-        if (s1 > s0) {
-            has_src = true;
-            for (int k = threadIdx.x; k < FC; k += NTB) ls[k] = T(0);
-            __syncthreads();
-            for (int k = s0 + threadIdx.x; k < s1; k += NTB) {
-                const int2 e = fs.ent[k];
-                ls[e.x] = fs.val[k];
-            }
-            __syncthreads();
-        }
-    }
-
-    // step 1 over the whole frame: every thread first issues the HBM loads of
-    // all its frame cells, then collides them into LDS layer 0
-    {
-        constexpr int C0 = (FC + NTB - 1) / NTB;
-        T fv0[C0][Q][1];
-        T cl0[C0];
-        T dl0[C0][2];
-        // frame coordinates wrap at most once when the box is at least a
-        // frame wide (no division); smaller boxes take the remainder
-        const bool wide = g.nx >= W && g.ny >= FH;
-#pragma unroll
-        for (int j = 0; j < C0; ++j) {
-            const int k = threadIdx.x + j * NTB;
-            if (k < FC) {
-                const int fx = k % W, fy = k / W;
-                int gx = x0 + fx, gy = y0 + fy;
-                if (wide) {
-                    gx = gx < 0 ? gx + g.nx : (gx >= g.nx ? gx - g.nx : gx);
-                    gy = gy < 0 ? gy + g.ny : (gy >= g.ny ? gy - g.ny : gy);
-                } else {
-                    gx %= g.nx;
-                    gy %= g.ny;
-                    if (gx < 0) gx += g.nx;
-                    if (gy < 0) gy += g.ny;
-                }
-                const Cell C = make_cell(g, gx, gy, 0);
-                if constexpr (O32) {
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-                        fv0[j][i][0] = at32(src + (int64_t)i * g.n, (unsigned)read_cell<2, R_PULL>(C, i));
-                    cl0[j] = at32(cl2a, (unsigned)C.c);
-                    if (MU) {
-                        dl0[j][0] = at32(dlnmu, (unsigned)C.c);
-                        dl0[j][1] = at32(dlnmu + g.n, (unsigned)C.c);
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) fv0[j][i][0] = src[(int64_t)i * g.n + read_cell<2, R_PULL>(C, i)];
-                    cl0[j] = cl2a[C.c];
-                    if (MU) {
-                        dl0[j][0] = dlnmu[C.c];
-                        dl0[j][1] = dlnmu[(int64_t)g.n + C.c];
-                    }
-                }
-            }
-        }
-        const T amp = has_src ? amps.a[0] : T(0);
-#pragma unroll
-        for (int j = 0; j < C0; ++j) {
-            const int k = threadIdx.x + j * NTB;
-            if (k < FC) {
-                T rho[1], K[2], Sp[1], o[Q][1];
-                moments<2, T>(fv0[j], rho, K);
-                Sp[0] = has_src ? ls[k] * amp : T(0);
-                if (MU) {
-                    add_mu_source<2, T>(K, cl0[j], dl0[j], Sp);
-                    ldl[0][k] = dl0[j][0];
-                    ldl[MU ? 1 : 0][k] = dl0[j][1];
-                }
-                collide<2, T>(fv0[j], cl0[j], Sp, has_src || MU, omega, TH || tau_half != 0, rho, K, o);
-                lc[k] = cl0[j];
-#pragma unroll
-                for (int i = 0; i < Q; ++i) lp[0][i][k] = o[i][0];
-            }
-        }
-        __syncthreads();
-    }
-
-    // steps 2..NS from LDS on shrinking regions; the last one writes the tile
-#pragma unroll
-    for (int st = 1; st < NS; ++st) {
-        const int r = H - st;               // region = tile grown by r
-        const int wr = TXF + 2 * r, hr = TY + 2 * r, off = H - r;
-        const T amp = has_src ? amps.a[st] : T(0);
-        const int in = (st - 1) % NB, out = st % NB;
-        for (int k = threadIdx.x; k < wr * hr; k += NTB) {
-            const int fx = off + k % wr, fy = off + k / wr;
-            const int f = fy * W + fx;
-            T fv[Q][1];
-            // pull from the previous layer: x - c_i in frame coordinates
-            fv[0][0] = lp[in][0][f];
-            fv[1][0] = lp[in][1][f - 1];
-            fv[2][0] = lp[in][2][f - W];
-            fv[3][0] = lp[in][3][f + 1];
-            fv[4][0] = lp[in][4][f + W];
-            const T cl2 = lc[f];
-            T rho[1], K[2], Sp[1];
-            moments<2, T>(fv, rho, K);
-            Sp[0] = has_src ? ls[f] * amp : T(0);
-            if (MU) {
-                const T dl[2] = {ldl[0][f], ldl[MU ? 1 : 0][f]};
-                add_mu_source<2, T>(K, cl2, dl, Sp);
-            }
-            T o[Q][1];
-            collide<2, T>(fv, cl2, Sp, has_src || MU, omega, TH || tau_half != 0, rho, K, o);
-            if (st == NS - 1) {
-                const int gx = x0 + fx, gy = y0 + fy;    // inside the tile: no wrap needed
-                if (gx < g.nx && gy < g.ny) {
-                    const int gcell = gx + g.nx * gy;
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) {
-                        if constexpr (O32) st_stream<NTS>(&at32(dst + (int64_t)i * g.n, (unsigned)gcell), o[i][0]);
-                        else st_stream<NTS>(&dst[(int64_t)i * g.n + gcell], o[i][0]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < Q; ++i) lp[out][i][f] = o[i][0];
-            }
-        }
-        if (st < NS - 1) __syncthreads();
-    }
-}
 
 // ---------------------------------------------------------------------------
 // 3D temporal blocking: two time steps per launch, marching along z

@@ -83,42 +83,46 @@ static void make_fused3_geo(lbem_s* h)
 
 static void make_fused_geo(lbem_s* h)
 {
-    h->fuse_nt = 256;
     if (h->D == 3) {
         make_fused3_geo(h);
         return;
     }
-    const bool f64 = h->prec == LBEM_F64;
-    // FP32: four steps per pass on 64 x 16 tiles of 512 threads, at every size.
-    // Measured, us per step, (steps, rows, threads): 2048^2 (2, 8, 256) 13.49,
-    // (4, 8, 256) 13.23, (4, 16, 256) 13.29, (4, 16, 512) 10.49; 1024^2 5.13 /
-    // 4.61 / 4.44 / 3.72; 512^2 2.45 / 1.85 / 2.29 / 1.65; 128^2 2.06 / 1.59 /
-    // 2.12 / 1.48; 4096^2 80.4 / 59.6 / 56.4 / 50.3; 8192^2 296 / 223 / 210 /
-    // 185.  The 512-thread block halves the frame per tile cell of the
-    // 256-thread 64 x 16 tile at the same two cells per thread.  With a varying
-    // mu the frame also stages grad ln mu, and the four-step 512-thread tile
-    // (86 KB of LDS) leaves one block per CU: two steps on 64 x 8 tiles there
-    // (2048^2, us per step: (2, 8, 256) 16.02, (2, 16, 512) 15.95, (4, 8, 256)
-    // 19.36, (4, 16, 512) 18.73).  FP64: two steps on 64 x 4 tiles.
-    const bool muv = h->cfg.mu_varies != 0;
-    h->fuse_ns = env_int("LBEM_FUSE", (f64 || muv) ? 2 : 4);
-    h->fuse_ty = env_int("LBEM_FUSE_TY", f64 ? 4 : (muv ? 8 : 16));
-    // only the instantiated (steps, rows, threads) triples; anything else runs
-    // single steps.  The thread count follows the (steps, rows) pair unless set.
-    const int ns = h->fuse_ns, ty = h->fuse_ty;
-    const bool pair512 = !f64 && ((ns == 2 && (ty == 16 || ty == 32)) || (ns == 4 && ty == 16));
-    h->fuse_nt = (!f64 && env_int("LBEM_FUSE_NT", pair512 ? 512 : 256) == 512) ? 512 : 256;
-    const bool ok = f64 ? ((ns == 2 && (ty == 8 || ty == 4)) || (ns == 3 && ty == 8))
-                  : h->fuse_nt == 512 ? ((ns == 2 && (ty == 16 || ty == 32)) || (ns == 4 && ty == 16))
-                        : ((ns == 2 && (ty == 16 || ty == 8 || ty == 4)) || (ns == 3 && ty == 16) ||
-                           (ns == 4 && (ty == 16 || ty == 8)));
-    if (!ok) h->fuse_ns = 1;
-    Geo& g = h->fgeo;
-    g = h->geo;
-    g.tiles_x = (g.nx + TXF - 1) / TXF;
-    g.tiles_y = (g.ny + h->fuse_ty - 1) / h->fuse_ty;
-    g.nblocks = g.tiles_x * g.tiles_y;
-    g.strip = 0;
+    // Four steps per launch, at every size, with or without a varying mu; calls
+    // for fewer steps take the launches of two and three.  Measured, us per
+    // step, two / three / four: the bytes per update fall with the steps and
+    // nothing else grows.
+    const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
+    h->fuse_ns = env_int("LBEM_FUSE", 4);
+    if (h->fuse_ns < 1 || h->fuse_ns > 4) h->fuse_ns = 1;
+    // FP32 lattices of 8e6 cells and more, rows of even length: two cells per
+    // lane.  One eighth of the columns is recomputed with one cell per lane,
+    // one sixteenth with two, which shows once the state streams from HBM (us
+    // per launch, one / two cells: 4096^2 180 / 171, 8192^2 694 / 645); below,
+    // twice as many waves with half the registers are as fast or faster
+    // (2048^2 31.8 / 32.2, 1000^2 10.8 / 12.9).  FP64 keeps one: two need more
+    // than 256 registers.
+    h->mcpl = h->prec == LBEM_F32 && nx % 2 == 0 && (double)h->n >= 8.0e6 ? 2 : 1;
+    MarchGeo& g = h->mgeo;
+    g.nx = nx; g.ny = ny; g.n = h->n;
+    const int ow = 64 * h->mcpl - 2 * MARCH_HX;
+    g.strips = (nx + ow - 1) / ow;
+    // Rows per chunk: whole rounds of the waves that are resident (four per
+    // SIMD with one cell per lane, two with two), about 24 rows each: a chunk
+    // reads 8 rows beyond its own, a thin last round leaves CUs idle.  FP32
+    // 2048^2, rows -> us per launch: 8 34.2, 16 33.4, 19 31.8 (3996 waves), 24
+    // 35.2, 40 31.8 (1924), 64 36.0.  Small lattices: as many waves as give
+    // two rows each, where a launch is a few rows of latency (256^2: 2 rows
+    // 4.2, 4 4.8, 8 5.9).
+    const int64_t slots = 1024 * (h->mcpl == 2 ? 2 : 4);
+    const int64_t want = std::max<int64_t>(1, ((int64_t)g.strips * ny + slots - 1) / slots);  // rows if all fit
+    const int64_t rounds = (want + 23) / 24;
+    const int64_t per = rounds * slots;
+    g.rows = (int)std::min<int64_t>(ny, std::max<int64_t>(2, ((int64_t)g.strips * ny + per - 1) / per));
+    g.nwork = g.strips * ((ny + g.rows - 1) / g.rows);
+    // few waves: one per block, so that they spread over the CUs (96x64 3.6
+    // against 4.0 us per launch)
+    h->mwpb = g.nwork <= 1024 ? 1 : 4;
+    g.nblocks = ((g.nwork + h->mwpb - 1) / h->mwpb + 7) / 8 * 8;
 }
 
 static void make_zmarch_geo(lbem_s* h)
@@ -425,6 +429,10 @@ static void free_source(lbem_s* h)
     if (h->fsrc_ent) (void)hipFree(h->fsrc_ent);
     if (h->fsrc_val) (void)hipFree(h->fsrc_val);
     h->src_off = nullptr; h->src_ent = nullptr; h->src_val = nullptr;
+    if (h->msrc_idx) (void)hipFree(h->msrc_idx);
+    if (h->msrc_val) (void)hipFree(h->msrc_val);
+    h->msrc_idx = nullptr; h->msrc_val = nullptr;
+    h->nmsrc = 0;
     if (h->zsrc_off) (void)hipFree(h->zsrc_off);
     if (h->zsrc_ent) (void)hipFree(h->zsrc_ent);
     if (h->zsrc_val) (void)hipFree(h->zsrc_val);
@@ -627,51 +635,56 @@ static int build_xrow_source(lbem_s* h, const std::vector<std::pair<int64_t, dou
     return LBEM_OK;
 }
 
-// Per-tile source entries of the fused 2D tiling: every frame cell (tile plus
-// halo, periodic images included) that carries a current.
-static int build_fused_source(lbem_s* h, const std::vector<double>& dense)
+// Source segments of the 2D strips: for every (strip, row) that holds source
+// cells the values of all its columns (periodic images included).
+static int build_march_source(lbem_s* h, const std::vector<std::pair<int64_t, double>>& cells)
 {
-    const Geo& g = h->fgeo;
-    const int H = h->fuse_ns - 1, TY = h->fuse_ty;
-    const int W = TXF + 2 * H, FH = TY + 2 * H;
-    std::vector<int> off(g.nblocks + 1, 0);
-    std::vector<int2> ent;
-    std::vector<double> val;
-    for (int b = 0; b < g.nblocks; ++b) {
-        const int tx = b % g.tiles_x, ty = b / g.tiles_x;
-        const int x0 = tx * TXF - H, y0 = ty * TY - H;
-        for (int fy = 0; fy < FH; ++fy) {
-            int gy = (y0 + fy) % g.ny;
-            if (gy < 0) gy += g.ny;
-            for (int fx = 0; fx < W; ++fx) {
-                int gx = (x0 + fx) % g.nx;
-                if (gx < 0) gx += g.nx;
-                const double v = dense[(size_t)gx + (size_t)g.nx * gy];
-                if (v != 0.0) {
-                    ent.push_back(make_int2(fy * W + fx, 0));
-                    val.push_back(v);
-                }
+    const MarchGeo& g = h->mgeo;
+    const int wid = 64 * h->mcpl, ow = wid - 2 * MARCH_HX;
+    std::vector<int> idx((size_t)g.strips * g.ny, -1);
+    for (int k = 0; k < 8; ++k) h->msrc_mask[k] = 0;
+    std::vector<double> val, row(g.nx, 0.0);
+    int segs = 0;
+    for (size_t k = 0; k < cells.size();) {        // cells are sorted: one row at a time
+        const int y = (int)(cells[k].first / g.nx);
+        size_t e = k;
+        for (; e < cells.size() && cells[e].first / g.nx == y; ++e) row[cells[e].first % g.nx] = cells[e].second;
+        for (int s = 0; s < g.strips; ++s) {
+            bool any = false;
+            int gx = (s * ow - MARCH_HX) % g.nx;
+            if (gx < 0) gx += g.nx;
+            const int gx0 = gx;
+            for (int j = 0; j < wid && !any; ++j) {
+                any = row[gx] != 0.0;
+                gx = gx + 1 == g.nx ? 0 : gx + 1;
+            }
+            if (!any) continue;
+            idx[(size_t)s * g.ny + y] = segs++;
+            h->msrc_mask[(s >> 5) & 7] |= 1u << (s & 31);
+            gx = gx0;
+            for (int j = 0; j < wid; ++j) {
+                val.push_back(row[gx]);
+                gx = gx + 1 == g.nx ? 0 : gx + 1;
             }
         }
-        off[b + 1] = (int)ent.size();
+        for (; k < e; ++k) row[cells[k].first % g.nx] = 0.0;
     }
-    const size_t ms = ent.size(), tv = h->prec == LBEM_F64 ? 8 : 4;
-    if (hipMalloc((void**)&h->fsrc_off, off.size() * sizeof(int)) != hipSuccess ||
-        hipMalloc((void**)&h->fsrc_ent, std::max<size_t>(ms, 1) * sizeof(int2)) != hipSuccess ||
-        hipMalloc((void**)&h->fsrc_val, std::max<size_t>(ms, 1) * tv) != hipSuccess)
+    if (!segs) return LBEM_OK;
+    const size_t tv = h->prec == LBEM_F64 ? 8 : 4;
+    if (hipMalloc((void**)&h->msrc_idx, idx.size() * sizeof(int)) != hipSuccess ||
+        hipMalloc((void**)&h->msrc_val, val.size() * tv) != hipSuccess)
         return LBEM_ENOMEM;
-    hipError_t e = hipMemcpy(h->fsrc_off, off.data(), off.size() * sizeof(int), hipMemcpyHostToDevice);
-    if (e == hipSuccess && ms) e = hipMemcpy(h->fsrc_ent, ent.data(), ms * sizeof(int2), hipMemcpyHostToDevice);
-    if (e == hipSuccess && ms) {
+    hipError_t e = hipMemcpy(h->msrc_idx, idx.data(), idx.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
         if (tv == 8) {
-            e = hipMemcpy(h->fsrc_val, val.data(), ms * 8, hipMemcpyHostToDevice);
+            e = hipMemcpy(h->msrc_val, val.data(), val.size() * 8, hipMemcpyHostToDevice);
         } else {
             std::vector<float> f(val.begin(), val.end());
-            e = hipMemcpy(h->fsrc_val, f.data(), ms * 4, hipMemcpyHostToDevice);
+            e = hipMemcpy(h->msrc_val, f.data(), f.size() * 4, hipMemcpyHostToDevice);
         }
     }
     if (e != hipSuccess) return LBEM_EDEVICE;
-    h->nfsrc = (int64_t)ms;
+    h->nmsrc = segs;
     return LBEM_OK;
 }
 
@@ -1005,9 +1018,16 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
     if (fused_format(h) && h->fuse_ns > 1) {
-        std::vector<double> dense((size_t)n, 0.0);
-        for (size_t k = 0; k < merged.size(); ++k) dense[(size_t)merged[k].first] = src_value[k];
-        const int rc = D == 2 ? build_fused_source(h, dense) : build_fused3_source(h, dense, pp);
+        int rc;
+        if (D == 2) {
+            std::vector<std::pair<int64_t, double>> cv(merged.size());
+            for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
+            rc = build_march_source(h, cv);
+        } else {
+            std::vector<double> dense((size_t)n, 0.0);
+            for (size_t k = 0; k < merged.size(); ++k) dense[(size_t)merged[k].first] = src_value[k];
+            rc = build_fused3_source(h, dense, pp);
+        }
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
     return LBEM_OK;
@@ -1021,10 +1041,13 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     const bool fuse = fused_ok(h);
     int64_t k = 0;
     while (k < nsteps) {
-        if (fuse && h->layout == LAYOUT_PULL_PENDING && nsteps - k >= h->fuse_ns) {
-            if (h->impl->step_fused(h, (amp && h->nsrc) ? amp + k : nullptr) != hipSuccess) return LBEM_EDEVICE;
-            k += h->fuse_ns;
-            h->t += h->fuse_ns;
+        // 2D launches take any number of steps from two to fuse_ns
+        const int64_t ns = std::min<int64_t>(h->fuse_ns, nsteps - k);
+        if (fuse && h->layout == LAYOUT_PULL_PENDING && (h->D == 2 ? ns >= 2 : ns == h->fuse_ns)) {
+            if (h->impl->step_fused(h, (amp && h->nsrc) ? amp + k : nullptr, (int)ns) != hipSuccess)
+                return LBEM_EDEVICE;
+            k += ns;
+            h->t += ns;
             continue;
         }
         const double a = (amp && h->nsrc) ? amp[k] : 0.0;

@@ -1,0 +1,341 @@
+// march2d.h -- 2D temporal blocking in registers: NS time steps per launch.
+//
+// One wave owns a strip of 64*CPL columns (CPL neighbouring cells per lane)
+// and a chunk of rows, and marches along the rows.  Iteration i reads row i of
+// the stored state once (level 0), and level s = 1..NS advances row i-s by its
+// s-th step from what level s-1 left in registers: the rest and +-x
+// populations of its previous row, the ones that move along the march of the
+// row before that (a ring of two) and the ones that move against it of the
+// row it has just made.  The +-x populations cross lanes by DPP wave shifts.
+// There is no LDS, no barrier and no frame addressing: every lane runs every
+// update, and the MARCH_HX columns at each end of the strip, whose neighbours
+// belong to other waves, are computed but not stored.  Ring indices are fixed
+// at compile time by unrolling four rows.  Neighbouring chunks march towards
+// and away from each other in turn, so that the rows both read are read at
+// about the same time and meet in one L2.  Each update is the single-step
+// kernel's arithmetic (moments, collide), so NS fused steps equal NS single
+// steps bit for bit.
+//
+// What bounds it: 21.5 VALU instructions per update (one cell, one step)
+// against 74 of the LDS-frame kernel it replaces, so the state's bytes do.
+// Measured per launch of four steps, LDS frame (64x16 tiles, 512 threads) ->
+// this kernel: FP32 2048^2 43.1 -> 31.8 us (44 B per cell and launch at 5.8
+// TB/s, Infinity Cache), 8192^2 740 -> 645 us (4.6 TB/s, the rate of a large
+// copy here), 96x64 5.5 -> 3.6 us (launch latency).
+#pragma once
+#include "kernels.h"
+
+namespace lbem {
+
+// the value of the lane before (dir > 0) or after (dir < 0); the end lane gets 0
+template <int DIR>
+__device__ __forceinline__ int lane_shift_b32(int v)
+{
+    // DPP wave_shr:1 / wave_shl:1
+    return __builtin_amdgcn_update_dpp(0, v, DIR > 0 ? 0x138 : 0x130, 0xf, 0xf, true);
+}
+template <int DIR, typename T>
+__device__ __forceinline__ T lane_shift(T v)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, lane_shift_b32<DIR>(__builtin_bit_cast(int, v)));
+    } else {
+        struct Two { int a, b; };
+        Two t = __builtin_bit_cast(Two, v);
+        t.a = lane_shift_b32<DIR>(t.a);
+        t.b = lane_shift_b32<DIR>(t.b);
+        return __builtin_bit_cast(T, t);
+    }
+}
+
+// Columns recomputed at each end of a strip, the same for every number of
+// steps, so that one source table serves them all.
+constexpr int MARCH_HX = 4;
+
+struct MarchGeo {
+    int nx, ny;
+    int strips;          // column strips of 64*CPL - 2*MARCH_HX stored columns
+    int rows;            // rows per chunk, at most 64 - 2*MARCH_HX
+    int nwork;           // strips * chunks
+    int nblocks;         // a multiple of 8: each XCD takes one contiguous range of work items
+    int64_t n;
+};
+
+// Sparse current source: idx[strip*ny + row] is the segment of that strip's
+// row (64*CPL values, S per unit amplitude, periodic images included) or -1.
+// Bit strip % 256 of mask is set for every strip that holds a source: the
+// others start without waiting for an index.
+template <typename T>
+struct MarchSrc {
+    const int* idx;
+    const T* val;
+    unsigned mask[8];    // all zero: no source
+};
+
+// CPL neighbouring elements at a byte offset off a scalar base.  A pair (FP32)
+// moves as one 8-byte access, aligned to 4 bytes.
+typedef float MarchPair __attribute__((ext_vector_type(2)));
+typedef MarchPair MarchPairU __attribute__((aligned(4)));
+template <typename S, int CPL>
+__device__ __forceinline__ void march_load(const S* base, unsigned off, S (&v)[CPL])
+{
+    const char* p = reinterpret_cast<const char*>(base) + off;
+    if constexpr (CPL == 1) {
+        v[0] = *reinterpret_cast<const S*>(p);
+    } else {
+        static_assert(CPL == 1 || std::is_same<S, float>::value, "pairs are FP32");
+        const MarchPair w = *reinterpret_cast<const MarchPairU*>(p);
+        v[0] = w[0];
+        v[1] = w[1];
+    }
+}
+template <typename S, int CPL>
+__device__ __forceinline__ void march_store(S* base, unsigned off, const S (&v)[CPL])
+{
+    char* p = reinterpret_cast<char*>(base) + off;
+    if constexpr (CPL == 1) {
+        *reinterpret_cast<S*>(p) = v[0];
+    } else {
+        static_assert(CPL == 1 || std::is_same<S, float>::value, "pairs are FP32");
+        const MarchPair w = {v[0], v[1]};
+        *reinterpret_cast<MarchPairU*>(p) = w;
+    }
+}
+
+// storage of the plain formats: five populations of type T per cell
+template <typename T_, int CPL>
+struct MarchPlain {
+    typedef T_ T;
+    const T* src;
+    T* dst;
+    int64_t n;
+    struct Raw { T v[5][CPL]; };
+    __device__ __forceinline__ void load(Raw& r, int64_t row, unsigned col) const
+    {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) march_load<T, CPL>(src + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
+    }
+    __device__ __forceinline__ void decode(const Raw& r, T (&o)[5][CPL]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) o[k][c] = r.v[k][c];
+    }
+    __device__ __forceinline__ void store(const Raw& r, int64_t row, unsigned col) const
+    {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            march_store<T, CPL>(dst + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
+    }
+};
+
+// One work item: strip x chunk.  SRC: the chunk holds source cells.
+template <class IO, int NS, int CPL, bool MU, bool TH, bool SRC, bool UP>
+__device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T* __restrict__ cl2a,
+                                             const typename IO::T* __restrict__ dlnmu, const MarchGeo& g,
+                                             const MarchSrc<typename IO::T>& ms,
+                                             const AmpPack<typename IO::T, NS>& amps,
+                                             const typename IO::T omega, const bool tau_half, const int strip,
+                                             const int y0, const int segs)
+{
+    typedef typename IO::T T;
+    constexpr int RING = 4, PF = 2;
+    static_assert(NS <= RING && NS <= MARCH_HX && RING % PF == 0, "ring indices repeat every RING rows");
+    constexpr int HX = MARCH_HX, OW = 64 * CPL - 2 * HX;
+    const int nx = g.nx, ny = g.ny;
+    const int lane = threadIdx.x & 63;
+    const int x0 = strip * OW;
+    // column of the lane's first cell, wrapped (any box width)
+    int gx = (x0 - HX + lane * CPL) % nx;
+    if (gx < 0) gx += nx;
+    const unsigned col0 = (unsigned)gx;
+    const int xo = x0 - HX + lane * CPL;         // unwrapped: stored if inside the strip's own columns
+    const bool keep = lane * CPL >= HX && lane * CPL < HX + OW && xo < nx;
+    const int rows = min(g.rows, ny - y0);
+    const int total = rows + 2 * NS;
+    int pr = (UP ? y0 + rows - 1 + NS : y0 - NS) % ny;   // next row to load, wrapped
+    if (pr < 0) pr += ny;
+
+    struct Row {
+        typename IO::Raw raw;
+        T cl[CPL];
+        T dl[MU ? 2 : 1][CPL];
+        T sv[CPL];
+    };
+    Row pf[PF];
+    T cl[RING][CPL], dl[MU ? RING : 1][2][CPL], sv[SRC ? RING : 1][CPL];
+    T a0[NS][CPL], a1[NS][CPL], a3[NS][CPL], a2[NS][2][CPL];
+
+    int nf = 0;                                  // rows fetched
+    auto fetch = [&](Row& r) {
+        const int64_t ro = (int64_t)pr * nx;
+        unsigned col = col0;
+        asm volatile("" : "+v"(col));            // keeps the 32-bit offset next to its loads (scalar-base form)
+        io.load(r.raw, ro, col);
+        march_load<T, CPL>(cl2a + ro, col * (unsigned)sizeof(T), r.cl);
+        if constexpr (MU) {
+            march_load<T, CPL>(dlnmu + ro, col * (unsigned)sizeof(T), r.dl[0]);
+            march_load<T, CPL>(dlnmu + g.n + ro, col * (unsigned)sizeof(T), r.dl[MU ? 1 : 0]);
+        }
+        if constexpr (SRC) {
+            const int seg = __builtin_amdgcn_readlane(segs, nf);   // lane k holds the segment of input row k
+            nf = nf + 1;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) r.sv[c] = T(0);
+            if (seg >= 0) {
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) r.sv[c] = ms.val[(int64_t)seg * (64 * CPL) + lane * CPL + c];
+            }
+        }
+        if constexpr (UP) pr = pr == 0 ? ny - 1 : pr - 1;
+        else pr = pr + 1 == ny ? 0 : pr + 1;
+    };
+
+    // iteration i (i % RING == U): level 0 and levels 1..LV
+    auto iter = [&](auto Uc, auto LVc, const int i) {
+        constexpr int U = decltype(Uc)::value, LV = decltype(LVc)::value;
+        Row& row = pf[U % PF];
+        T o[5][CPL];
+        io.decode(row.raw, o);
+        T clnew[CPL], dlnew[2][CPL], svnew[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            clnew[c] = row.cl[c];
+            if constexpr (MU) {
+                dlnew[0][c] = row.dl[0][c];
+                dlnew[1][c] = row.dl[MU ? 1 : 0][c];
+            }
+            if constexpr (SRC) svnew[c] = row.sv[c];
+        }
+        if (i + PF < total) fetch(row);
+#pragma unroll
+        for (int s = 1; s <= NS; ++s) {
+            if (s > LV + 1) continue;
+            T f[CPL][5][1];
+            if (s <= LV) {
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    f[c][0][0] = a0[s - 1][c];
+                    f[c][1][0] = c > 0 ? a1[s - 1][c > 0 ? c - 1 : 0] : lane_shift<1>(a1[s - 1][CPL - 1]);
+                    f[c][3][0] = c < CPL - 1 ? a3[s - 1][c < CPL - 1 ? c + 1 : 0] : lane_shift<-1>(a3[s - 1][0]);
+                    f[c][UP ? 4 : 2][0] = a2[s - 1][U & 1][c];
+                    f[c][UP ? 2 : 4][0] = o[UP ? 2 : 4][c];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                a0[s - 1][c] = o[0][c];
+                a1[s - 1][c] = o[1][c];
+                a3[s - 1][c] = o[3][c];
+                a2[s - 1][U & 1][c] = o[UP ? 4 : 2][c];
+            }
+            if (s <= LV) {
+                constexpr int R4 = RING;
+                const int q = (U + R4 - s % R4) % R4;     // ring slot of row i - s
+                const int64_t orow = (int64_t)(UP ? y0 + rows - 1 - (i - 2 * NS) : y0 + i - 2 * NS) * nx;
+                typename IO::Raw st;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    T rho[1], K[2], Sp[1];
+                    moments<2, T>(f[c], rho, K);
+                    Sp[0] = SRC ? sv[SRC ? q : 0][c] * amps.a[s - 1] : T(0);
+                    if constexpr (MU) {
+                        const T d2[2] = {dl[MU ? q : 0][0][c], dl[MU ? q : 0][1][c]};
+                        add_mu_source<2, T>(K, cl[q][c], d2, Sp);
+                    }
+                    T out[5][1];
+                    collide<2, T>(f[c], cl[q][c], Sp, SRC || MU, omega, TH || tau_half, rho, K, out);
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) {
+                        if (s == NS) st.v[k][c] = out[k][0];
+                        else o[k][c] = out[k][0];
+                    }
+                }
+                if (s == NS && keep) {
+                    unsigned xc = (unsigned)xo;
+                    asm volatile("" : "+v"(xc));
+                    io.store(st, orow, xc);
+                }
+            }
+        }
+        // row i's coefficients replace row i - RING's
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            cl[U][c] = clnew[c];
+            if constexpr (MU) {
+                dl[MU ? U : 0][0][c] = dlnew[0][c];
+                dl[MU ? U : 0][1][c] = dlnew[1][c];
+            }
+            if constexpr (SRC) sv[SRC ? U : 0][c] = svnew[c];
+        }
+    };
+#define LBEM_IC(v) std::integral_constant<int, (v)>{}
+#pragma unroll
+    for (int k = 0; k < PF; ++k) fetch(pf[k]);
+    // the first 2 NS rows fill the levels one after another
+    iter(LBEM_IC(0), LBEM_IC(0), 0);
+    iter(LBEM_IC(1), LBEM_IC(0), 1);
+    iter(LBEM_IC(2), LBEM_IC(1), 2);
+    iter(LBEM_IC(3), LBEM_IC(1), 3);
+    if constexpr (NS >= 3) {
+        iter(LBEM_IC(0), LBEM_IC(2), 4);
+        iter(LBEM_IC(1), LBEM_IC(2), 5);
+    }
+    if constexpr (NS >= 4) {
+        iter(LBEM_IC(2), LBEM_IC(3), 6);
+        iter(LBEM_IC(3), LBEM_IC(3), 7);
+    }
+    int i = 2 * NS;
+    while (true) {
+        iter(LBEM_IC((2 * NS) % RING), LBEM_IC(NS), i);
+        if (++i >= total) break;
+        iter(LBEM_IC((2 * NS + 1) % RING), LBEM_IC(NS), i);
+        if (++i >= total) break;
+        iter(LBEM_IC((2 * NS + 2) % RING), LBEM_IC(NS), i);
+        if (++i >= total) break;
+        iter(LBEM_IC((2 * NS + 3) % RING), LBEM_IC(NS), i);
+        if (++i >= total) break;
+    }
+#undef LBEM_IC
+}
+
+template <class IO, int NS, int CPL, bool MU, bool TH>
+__global__ __launch_bounds__(NT) void k_march2d(const IO io, const typename IO::T* __restrict__ cl2a,
+                                               const typename IO::T* __restrict__ dlnmu, const MarchGeo g,
+                                               const MarchSrc<typename IO::T> ms,
+                                               const AmpPack<typename IO::T, NS> amps,
+                                               const typename IO::T omega, const int tau_half)
+{
+    const int b = remap_block(blockIdx.x, g.nblocks, 1);
+    const int w = __builtin_amdgcn_readfirstlane(b * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6));
+    if (w >= g.nwork) return;
+    const int strip = w % g.strips, y0 = (w / g.strips) * g.rows;
+    unsigned m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = ((strip >> 5) & 7) == k ? ms.mask[k] : m;
+    bool src = false;
+    int segs = -1;
+    if ((m >> (strip & 31)) & 1u) {
+        // the segments of the rows this item reads (at most 64), one per lane
+        const int k = threadIdx.x & 63;
+        if (k < min(g.rows, g.ny - y0) + 2 * NS) {
+            int r = (y0 - NS + k) % g.ny;
+            if (r < 0) r += g.ny;
+            segs = ms.idx[strip * g.ny + r];
+        }
+        src = __any(segs >= 0);
+    }
+    const bool up = (w / g.strips) & 1;
+    if (src)
+        march2d_item<IO, NS, CPL, MU, TH, true, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
+                                                       segs);
+    else if (up)
+        march2d_item<IO, NS, CPL, MU, TH, false, true>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
+                                                       segs);
+    else
+        march2d_item<IO, NS, CPL, MU, TH, false, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
+                                                       segs);
+}
+
+}  // namespace lbem
