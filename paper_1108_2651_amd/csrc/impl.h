@@ -345,7 +345,9 @@ static void launch_march(lbem_s* h, const IO& io, const double* amp)
 template <class IO, int NS, int CPL, bool MU>
 static void launch_march_th(lbem_s* h, const IO& io, const double* amp)
 {
-    if (h->cfg.tau == 0.5) launch_march<IO, NS, CPL, MU, true>(h, io, amp);
+    // (the 16-bit formats scale by one factor either way)
+    if constexpr (IO::DEV) launch_march<IO, NS, CPL, MU, false>(h, io, amp);
+    else if (h->cfg.tau == 0.5) launch_march<IO, NS, CPL, MU, true>(h, io, amp);
     else launch_march<IO, NS, CPL, MU, false>(h, io, amp);
 }
 
@@ -419,9 +421,8 @@ static hipError_t go_fused3(lbem_s* h, const T* src, T* dst, const double* amp)
     return h->nts ? go_fused3_n<T, true>(h, src, dst, amp) : go_fused3_n<T, false>(h, src, dst, amp);
 }
 
-// formats with a multi-step kernel: the plain FP32/FP64 ones, and the 3D
-// deviation formats (two steps)
-static bool fused_format(const lbem_s* h) { return h->prec <= LBEM_F32 || (is_dev(h->prec) && h->D == 3); }
+// formats with a multi-step kernel: all but plain FP16
+static bool fused_format(const lbem_s* h) { return h->prec <= LBEM_F32 || is_dev(h->prec); }
 
 static bool fused_ok(const lbem_s* h)
 {
@@ -699,7 +700,10 @@ struct DevImpl : Impl {
             h->cur = to;
             return hipGetLastError();
         } else {
-            return hipErrorInvalidValue;
+            typedef MarchDev<H, GH, 1> IO;
+            const int from = h->cur, to = 1 - h->cur;
+            h->cur = to;
+            return go_march<IO, 1>(h, IO{M(h, from), Dv(h, from), M(h, to), Dv(h, to), h->n}, amp, ns);
         }
     }
     hipError_t fields(lbem_s* h, double* E, double* B, double* partials) override

@@ -1061,8 +1061,10 @@ __device__ __forceinline__ void dev_store(const float (&out)[Lat<D>::Q][Lat<D>::
 // the new state from their equilibrium is (1 - omega)(g - g0(m)) exactly.
 // Only that product is rounded; the post-collision populations are never
 // formed and their moments never summed again.  M receives the stored FP32
-// moments, code the stored 16-bit codes (slot order).
-template <int D, typename H, bool GH>
+// moments, code the stored 16-bit codes (slot order).  RW: wc0 holds its
+// reciprocal instead (a caller that keeps 1/wc0 over several steps saves the
+// division; the scale is a power of two, so the product has the quotient's bits).
+template <int D, typename H, bool GH, bool RW = false>
 __device__ __forceinline__ void dev_encode(const float (&f)[Lat<D>::Q][Lat<D>::P], float cl2, float wc0,
                                            const float (&Sp)[Lat<D>::P], bool any_src, float omega, bool tau_half,
                                            const float (&rho)[Lat<D>::P], const float (&K)[D],
@@ -1097,7 +1099,7 @@ __device__ __forceinline__ void dev_encode(const float (&f)[Lat<D>::Q][Lat<D>::P
             const int sl = dev_slot<D, GH>(i, p);
             if (sl < 0) continue;
             float c;
-            if (i == 0) c = (f[0][p] - (rho[p] - float(D) * Lam[p])) * (f1 * (inv / wc0));
+            if (i == 0) c = (f[0][p] - (rho[p] - float(D) * Lam[p])) * (f1 * (RW ? inv * wc0 : inv / wc0));
             else c = (f[i][p] - 0.5f * twice_eq_moving<D, float>(i, p, Lam[p], Bb)) * km;
             code[sl] = f2h<H>(sat16<H>(c));
         }

@@ -87,10 +87,10 @@ static void make_fused_geo(lbem_s* h)
         make_fused3_geo(h);
         return;
     }
-    // Four steps per launch, at every size, with or without a varying mu; calls
-    // for fewer steps take the launches of two and three.  Measured, us per
-    // step, two / three / four: the bytes per update fall with the steps and
-    // nothing else grows.
+    // Four steps per launch in every format but plain FP16, at every size, with
+    // or without a varying mu (the bytes per update fall with the steps and
+    // nothing else grows); calls for fewer steps take the launches of two and
+    // three.
     const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
     h->fuse_ns = env_int("LBEM_FUSE", 4);
     if (h->fuse_ns < 1 || h->fuse_ns > 4) h->fuse_ns = 1;

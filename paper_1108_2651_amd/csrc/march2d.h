@@ -14,14 +14,21 @@
 // and away from each other in turn, so that the rows both read are read at
 // about the same time and meet in one L2.  Each update is the single-step
 // kernel's arithmetic (moments, collide), so NS fused steps equal NS single
-// steps bit for bit.
+// steps bit for bit.  In the 16-bit formats level 0 decodes each stored cell
+// once, where the per-cell kernel decodes every neighbour, and a level between
+// the first and the last step encodes its result as it would be stored and
+// decodes that in registers, as every reader would.
 //
 // What bounds it: 21.5 VALU instructions per update (one cell, one step)
 // against 74 of the LDS-frame kernel it replaces, so the state's bytes do.
 // Measured per launch of four steps, LDS frame (64x16 tiles, 512 threads) ->
 // this kernel: FP32 2048^2 43.1 -> 31.8 us (44 B per cell and launch at 5.8
 // TB/s, Infinity Cache), 8192^2 740 -> 645 us (4.6 TB/s, the rate of a large
-// copy here), 96x64 5.5 -> 3.6 us (launch latency).
+// copy here), 96x64 5.5 -> 3.6 us (launch latency).  16-bit formats, per step,
+// one step per launch of the per-cell kernel -> four of this one: 3000x2500
+// FP16-dev 113 -> 32 us (12 B per update at 2.8 TB/s: VALU bound, about 90
+// instructions per update for encoding and decoding), FP16 ghost 20 us.  They
+// take one cell per lane (two need more than 256 registers: 32 against 37 us).
 #pragma once
 #include "kernels.h"
 
@@ -110,12 +117,13 @@ struct MarchPlain {
     T* dst;
     int64_t n;
     struct Raw { T v[5][CPL]; };
+    static constexpr bool DEV = false, REST = false;
     __device__ __forceinline__ void load(Raw& r, int64_t row, unsigned col) const
     {
 #pragma unroll
         for (int k = 0; k < 5; ++k) march_load<T, CPL>(src + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
     }
-    __device__ __forceinline__ void decode(const Raw& r, T (&o)[5][CPL]) const
+    __device__ __forceinline__ void decode(const Raw& r, const T (&)[CPL], T (&o)[5][CPL]) const
     {
 #pragma unroll
         for (int k = 0; k < 5; ++k)
@@ -127,6 +135,64 @@ struct MarchPlain {
 #pragma unroll
         for (int k = 0; k < 5; ++k)
             march_store<T, CPL>(dst + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
+    }
+};
+
+// storage of the 16-bit formats: three FP32 moments and the codes
+template <typename H, bool GH, int CPL>
+struct MarchDev {
+    typedef float T;
+    typedef H Code;
+    static constexpr bool GHOST = GH;
+    static constexpr int NC = DevSlots<2, GH>::N;
+    const float* Min;
+    const H* Din;
+    float* Mout;
+    H* Dout;
+    int64_t n;
+    struct Raw { float m[3][CPL]; H c[NC][CPL]; };
+    static constexpr bool DEV = true, REST = !GH;
+    __device__ __forceinline__ void load(Raw& r, int64_t row, unsigned col) const
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) march_load<float, CPL>(Min + (int64_t)k * n + row, col * 4u, r.m[k]);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) march_load<H, CPL>(Din + (int64_t)k * n + row, col * 2u, r.c[k]);
+    }
+    // the five populations of a cell from its stored moments and codes, as dev_load forms them
+    static __device__ __forceinline__ void pops(const float (&m)[3], const H (&code)[NC], float wc0, float (&o)[5])
+    {
+        float mag = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) mag = fmaxf(mag, fabsf(m[k]));
+        float s, inv;
+        pow2_scale(mag, s, inv);
+        const float Lam[1] = {m[0]}, Bb[2] = {m[1], m[2]};
+        auto get = [&](int sl) { return h2f<H>(code[sl]); };
+#pragma unroll
+        for (int i = 0; i < 5; ++i) o[i] = dev_eq<2>(i, 0, Lam, Bb, wc0) + dev_value_of<2, GH>(get, i, 0, s, wc0);
+    }
+    __device__ __forceinline__ void decode(const Raw& r, const float (&wc0)[CPL], float (&o)[5][CPL]) const
+    {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            float m[3], v[5];
+            H cd[NC];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) m[k] = r.m[k][c];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) cd[k] = r.c[k][c];
+            pops(m, cd, wc0[c], v);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) o[k][c] = v[k];
+        }
+    }
+    __device__ __forceinline__ void store(const Raw& r, int64_t row, unsigned col) const
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) march_store<float, CPL>(Mout + (int64_t)k * n + row, col * 4u, r.m[k]);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) march_store<H, CPL>(Dout + (int64_t)k * n + row, col * 2u, r.c[k]);
     }
 };
 
@@ -164,7 +230,9 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
         T sv[CPL];
     };
     Row pf[PF];
-    T cl[RING][CPL], dl[MU ? RING : 1][2][CPL], sv[SRC ? RING : 1][CPL];
+    constexpr bool WC = IO::DEV;                 // w0/c^2 is kept per row
+    constexpr bool RW = IO::REST;                // and its reciprocal (stored rest codes)
+    T cl[RING][CPL], wc[WC ? RING : 1][CPL], rw[RW ? RING : 1][CPL], dl[MU ? RING : 1][2][CPL], sv[SRC ? RING : 1][CPL];
     T a0[NS][CPL], a1[NS][CPL], a3[NS][CPL], a2[NS][2][CPL];
 
     int nf = 0;                                  // rows fetched
@@ -196,8 +264,11 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
     auto iter = [&](auto Uc, auto LVc, const int i) {
         constexpr int U = decltype(Uc)::value, LV = decltype(LVc)::value;
         Row& row = pf[U % PF];
+        T wnew[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) wnew[c] = WC ? T(1) / row.cl[c] - T(2) : T(0);
         T o[5][CPL];
-        io.decode(row.raw, o);
+        io.decode(row.raw, wnew, o);
         T clnew[CPL], dlnew[2][CPL], svnew[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
@@ -244,12 +315,31 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                         const T d2[2] = {dl[MU ? q : 0][0][c], dl[MU ? q : 0][1][c]};
                         add_mu_source<2, T>(K, cl[q][c], d2, Sp);
                     }
-                    T out[5][1];
-                    collide<2, T>(f[c], cl[q][c], Sp, SRC || MU, omega, TH || tau_half, rho, K, out);
+                    if constexpr (IO::DEV) {
+                        float M[3];
+                        typename IO::Code cd[IO::NC];
+                        dev_encode<2, typename IO::Code, IO::GHOST, RW>(f[c], cl[q][c], RW ? rw[RW ? q : 0][c] : wc[q][c],
+                                                                        Sp, SRC || MU, omega, TH || tau_half, rho, K,
+                                                                        M, cd);
+                        if (s == NS) {
 #pragma unroll
-                    for (int k = 0; k < 5; ++k) {
-                        if (s == NS) st.v[k][c] = out[k][0];
-                        else o[k][c] = out[k][0];
+                            for (int k = 0; k < 3; ++k) st.m[k][c] = M[k];
+#pragma unroll
+                            for (int k = 0; k < IO::NC; ++k) st.c[k][c] = cd[k];
+                        } else {
+                            float v[5];
+                            IO::pops(M, cd, wc[q][c], v);
+#pragma unroll
+                            for (int k = 0; k < 5; ++k) o[k][c] = v[k];
+                        }
+                    } else {
+                        T out[5][1];
+                        collide<2, T>(f[c], cl[q][c], Sp, SRC || MU, omega, TH || tau_half, rho, K, out);
+#pragma unroll
+                        for (int k = 0; k < 5; ++k) {
+                            if (s == NS) st.v[k][c] = out[k][0];
+                            else o[k][c] = out[k][0];
+                        }
                     }
                 }
                 if (s == NS && keep) {
@@ -263,6 +353,8 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
             cl[U][c] = clnew[c];
+            if constexpr (WC) wc[WC ? U : 0][c] = wnew[c];
+            if constexpr (RW) rw[RW ? U : 0][c] = T(1) / wnew[c];
             if constexpr (MU) {
                 dl[MU ? U : 0][0][c] = dlnew[0][c];
                 dl[MU ? U : 0][1][c] = dlnew[1][c];

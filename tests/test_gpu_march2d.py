@@ -1,5 +1,6 @@
 """2D multi-step launches (register march over column strips and row chunks):
-two, three and four steps per launch equal single steps bit for bit at the
+two, three and four steps per launch equal single steps bit for bit, in every
+format that has them, fields and stored state, at the
 edges of the strips (56 stored columns of 64, or 120 of 128 for large FP32
 lattices with rows of even length) and of the chunks, with sources whose
 periodic images fall into several strips, the mu term, general tau, and call
@@ -21,7 +22,7 @@ def same(a, b):
     return ok
 
 
-@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("prec", ["f32", "f64", "f16dev", "bf16dev", "f16ghost", "bf16ghost"])
 @pytest.mark.parametrize("shape", [(55, 9, 1), (56, 1, 1), (57, 3, 1), (64, 25, 1), (113, 48, 1), (3, 70, 1)])
 @pytest.mark.parametrize("mu", [False, True])
 def test_strip_and_chunk_edges(prec, shape, mu):
@@ -32,6 +33,7 @@ def test_strip_and_chunk_edges(prec, shape, mu):
             ref = gpu_run(p, steps, prec, "pull", tau=tau, env={"LBEM_FUSE": 1})
             got = gpu_run(p, steps, prec, "pull", tau=tau)
             assert ref.steps_per_launch == 1 and got.steps_per_launch == 4
+            assert np.array_equal(got.get_state(), ref.get_state()), (prec, shape, steps, tau)
             assert same(got, ref), (prec, shape, steps, tau)
 
 
