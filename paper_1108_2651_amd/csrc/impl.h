@@ -15,6 +15,7 @@
 #include "../../include/lbem.h"
 #include "kernels.h"
 #include "march2d.h"
+#include "pair3d.h"
 
 using namespace lbem;
 
@@ -157,6 +158,13 @@ struct lbem_s {
     int64_t nmsrc;       // source segments of the strips
     int f3_tx, f3_ty, f3_lz;
     Geo fgeo;
+    // 3D 16-bit formats: two steps per launch (k_pair_dev3) and its source
+    // segments
+    PairGeo pgeo;
+    unsigned char* psrc_flag;
+    int* psrc_idx;
+    float* psrc_val;
+    int psrc_pair;
     int* fsrc_off;
     int2* fsrc_ent;
     void* fsrc_val;
@@ -680,23 +688,20 @@ struct DevImpl : Impl {
     hipError_t step_fused(lbem_s* h, const double* amp, int ns) override
     {
         if constexpr (D == 3) {
-            FusedSrc<float> fs;
-            fs.off = h->nfsrc ? h->fsrc_off : nullptr;
-            fs.ent = h->fsrc_ent;
-            fs.val = (const float*)h->fsrc_val;
+            const PairSrc ps{h->psrc_flag, h->psrc_idx, h->psrc_val, h->psrc_pair};
             AmpPack<float, 2> a;
             for (int j = 0; j < 2; ++j) a.a[j] = (float)(amp ? amp[j] : 0.0);
             const int from = h->cur, to = 1 - h->cur;
+            const float om = (float)(1.0 / h->cfg.tau);
+            const int th = h->cfg.tau == 0.5;
             if (h->mu_set)
-                hipLaunchKernelGGL((k_step_dev3f<H, GH, true>), dim3(h->fgeo.nblocks), dim3(NT), 0, h->stream,
+                hipLaunchKernelGGL((k_pair_dev3<H, GH, true>), dim3(h->pgeo.nblocks), dim3(1024), 0, h->stream,
                                    M(h, from), Dv(h, from), M(h, to), Dv(h, to), (const float*)h->cl2,
-                                   (const float*)h->dlnmu, h->fgeo, h->f3_lz, fs, a, (float)(1.0 / h->cfg.tau),
-                                   (int)(h->cfg.tau == 0.5));
+                                   (const float*)h->dlnmu, h->pgeo, ps, a, om, th);
             else
-                hipLaunchKernelGGL((k_step_dev3f<H, GH, false>), dim3(h->fgeo.nblocks), dim3(NT), 0, h->stream,
+                hipLaunchKernelGGL((k_pair_dev3<H, GH, false>), dim3(h->pgeo.nblocks), dim3(1024), 0, h->stream,
                                    M(h, from), Dv(h, from), M(h, to), Dv(h, to), (const float*)h->cl2,
-                                   (const float*)h->dlnmu, h->fgeo, h->f3_lz, fs, a, (float)(1.0 / h->cfg.tau),
-                                   (int)(h->cfg.tau == 0.5));
+                                   (const float*)h->dlnmu, h->pgeo, ps, a, om, th);
             h->cur = to;
             return hipGetLastError();
         } else {

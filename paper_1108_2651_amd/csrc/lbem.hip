@@ -52,11 +52,6 @@ static void make_fused3_geo(lbem_s* h)
     const bool small = (double)h->n < FUSE3D_MIN;
     h->fuse_ns = env_int("LBEM_FUSE3", (f64 || small) ? 1 : 2) == 2 ? 2 : 1;
     h->f3_tx = env_int("LBEM_FUSE3_TX", f64 ? 32 : 64) == 64 && !f64 ? 64 : 32;
-    if (is_dev(h->prec)) {
-        // the two-step deviation kernel (64 x 4 column tiles)
-        h->fuse_ns = env_int("LBEM_DEV3F", 0) ? 2 : 1;
-        h->f3_tx = 64;
-    }
     h->f3_ty = NT / h->f3_tx;
     // FP32 64-wide tiles take 8 rows: 512 threads, two blocks per CU (80 KB of
     // LDS, <= 128 VGPRs), and step 1 runs on a frame of 1.29x the tile instead
@@ -81,8 +76,58 @@ static void make_fused3_geo(lbem_s* h)
     g.xcd = env_int("LBEM_FUSE3_XCD", 32);
 }
 
+static int device_cus()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+        return v;
+    return 256;
+}
+
+// Two steps per launch for the 3D 16-bit formats (k_pair_dev3): tiles of 60 x
+// 12 stored cells, one block per CU, chunks of lz planes.
+static void make_pair_geo(lbem_s* h)
+{
+    PairGeo& g = h->pgeo;
+    g.nx = (int)h->cfg.nx; g.ny = (int)h->cfg.ny; g.nz = (int)h->cfg.nz; g.n = h->n;
+    g.tiles_x = (g.nx + PRX - 1) / PRX;
+    g.tiles_y = (g.ny + PRY - 1) / PRY;
+    // The chunk length with the least work: rounds of resident blocks times the
+    // planes of a chunk, four of which only fill the pipeline.
+    const int64_t cus = device_cus(), cols = (int64_t)g.tiles_x * g.tiles_y;
+    int64_t best = -1;
+    for (int c = 1; c <= g.nz; ++c) {
+        const int lz = (g.nz + c - 1) / c, chunks = (g.nz + lz - 1) / lz;
+        const int64_t cost = (cols * chunks + cus - 1) / cus * (lz + 4);
+        if (best < 0 || cost < best) { best = cost; g.lz = lz; }
+        if (lz <= 4) break;
+    }
+    g.lz = std::max(1, env_int("LBEM_FUSE3_LZ", g.lz));
+    g.nblocks = (int)(cols * ((g.nz + g.lz - 1) / g.lz));
+    g.xcd = env_int("LBEM_FUSE3_XCD", std::max(2, g.tiles_x));
+    // Taken where enough of the work is on stored cells: n over (rounds * CUs *
+    // planes of a chunk * 720) of at least 0.28 with ghost coordinates, 0.36
+    // with all deviations, 0.09 more where rows are whole 64-cell lines, which
+    // the single steps read without a split.  Measured, us per step, single /
+    // pair (share): FP16 ghost 64^3 (0.18) 8.6 / 12.7, 61x100x100 (0.28) 19.4 /
+    // 20.1, 88^3 (0.37) 22.5 / 16.4, 64x128x128 (0.36) 25.3 / 25.2, 128^3
+    // (0.50) 46.2 / 35.9, 160^3 105 / 72, 256^3 370 / 316, 250x190x171 274 /
+    // 133; FP16-dev 80^3 (0.31) 16.8 / 17.2, 88^3 22.8 / 19.5, 64x256x256
+    // (0.41) 115 / 125, 128^3 62.5 / 51.5, 256^3 438 / 374, 250x190x171 358 /
+    // 163; with a varying mu 256^3 423 / 353 and 481 / 405.
+    const double share = (double)g.n / ((double)((g.nblocks + cus - 1) / cus) * cus * (g.lz + 4) * (PRX * PRY));
+    const bool ghost = h->prec == LBEM_F16GHOST || h->prec == LBEM_BF16GHOST;
+    const double need = (ghost ? 0.28 : 0.36) + (g.nx % 64 == 0 ? 0.09 : 0.0);
+    h->fuse_ns = env_int("LBEM_DEV3F", share >= need) ? 2 : 1;
+}
+
 static void make_fused_geo(lbem_s* h)
 {
+    if (h->D == 3 && is_dev(h->prec)) {
+        make_pair_geo(h);
+        return;
+    }
     if (h->D == 3) {
         make_fused3_geo(h);
         return;
@@ -203,11 +248,7 @@ static void make_row_geo(lbem_s* h)
     // twice: FP16 ghost, planes -> us per step, 192^3 (5 rows) 3 166, 5 166,
     // 6 176, 7 190; 160^3 (6 rows) 3 106, 4 120, 5 109; 144^3 (7 rows) 2 88,
     // 3 107; 512^3 (2 rows) 7 2909-2913, 8 2917-2925, 16 2945.
-    int cus = 256, dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-        cus = v;
-    const int64_t slots = (int64_t)cus * (1024 / ntb);
+    const int64_t slots = (int64_t)device_cus() * (1024 / ntb);
     const int tymax = std::max(1, 2 * ntb / nx);
     g.ty = std::max(1, std::min(tymax, env_int("LBEM_DEV3R_TY", tymax)));
     g.tiles_y = (ny + g.ty - 1) / g.ty;
@@ -433,6 +474,10 @@ static void free_source(lbem_s* h)
     if (h->msrc_val) (void)hipFree(h->msrc_val);
     h->msrc_idx = nullptr; h->msrc_val = nullptr;
     h->nmsrc = 0;
+    if (h->psrc_flag) (void)hipFree(h->psrc_flag);
+    if (h->psrc_idx) (void)hipFree(h->psrc_idx);
+    if (h->psrc_val) (void)hipFree(h->psrc_val);
+    h->psrc_flag = nullptr; h->psrc_idx = nullptr; h->psrc_val = nullptr;
     if (h->zsrc_off) (void)hipFree(h->zsrc_off);
     if (h->zsrc_ent) (void)hipFree(h->zsrc_ent);
     if (h->zsrc_val) (void)hipFree(h->zsrc_val);
@@ -632,6 +677,62 @@ static int build_xrow_source(lbem_s* h, const std::vector<std::pair<int64_t, dou
     }
     if (e != hipSuccess) return LBEM_EDEVICE;
     h->nxsrc = (int64_t)ms;
+    return LBEM_OK;
+}
+
+// Source segments of the pair tiling: for every (tile column, plane, row) that
+// holds source cells the values of its 64 columns (periodic images included),
+// and per block whether any row it updates does.
+static int build_pair_source(lbem_s* h, const std::vector<std::pair<int64_t, double>>& cells, int pp)
+{
+    const PairGeo& g = h->pgeo;
+    const size_t plane = (size_t)g.ny * g.nz;
+    std::vector<int> idx((size_t)g.tiles_x * plane, -1);
+    std::vector<unsigned char> flag((size_t)g.nblocks, 0);
+    // per row and plane the tiles and chunks whose frame (the stored rows and
+    // planes and two more on each side, periodic images included) holds it
+    auto frames = [](int n, int step, int count) {
+        std::vector<std::vector<int>> of(n);
+        for (int t = 0; t < count; ++t)
+            for (int j = 0; j < std::min(n, step + 4); ++j) of[(((t * step - 2 + j) % n) + n) % n].push_back(t);
+        return of;
+    };
+    const auto tiles = frames(g.ny, PRY, g.tiles_y), chunks = frames(g.nz, g.lz, (g.nz + g.lz - 1) / g.lz);
+    std::vector<float> val, row(g.nx, 0.f);
+    int segs = 0;
+    for (size_t k = 0; k < cells.size();) {        // cells are sorted: one row at a time
+        const int64_t r = cells[k].first / g.nx;   // row index y + ny z
+        const int y = (int)(r % g.ny), z = (int)(r / g.ny);
+        size_t e = k;
+        for (; e < cells.size() && cells[e].first / g.nx == r; ++e) row[cells[e].first % g.nx] = (float)cells[e].second;
+        for (int t = 0; t < g.tiles_x; ++t) {
+            int gx = (t * PRX - 2) % g.nx;
+            if (gx < 0) gx += g.nx;
+            float seg[64];
+            bool any = false;
+            for (int j = 0; j < 64; ++j) {
+                seg[j] = row[gx];
+                any = any || seg[j] != 0.f;
+                gx = gx + 1 == g.nx ? 0 : gx + 1;
+            }
+            if (!any) continue;
+            idx[(size_t)t * plane + (size_t)z * g.ny + y] = segs++;
+            val.insert(val.end(), seg, seg + 64);
+            for (int ty : tiles[y])
+                for (int zc : chunks[z]) flag[((size_t)zc * g.tiles_y + ty) * g.tiles_x + t] = 1;
+        }
+        for (; k < e; ++k) row[cells[k].first % g.nx] = 0.f;
+    }
+    if (!segs) return LBEM_OK;
+    if (hipMalloc((void**)&h->psrc_idx, idx.size() * sizeof(int)) != hipSuccess ||
+        hipMalloc((void**)&h->psrc_val, val.size() * sizeof(float)) != hipSuccess ||
+        hipMalloc((void**)&h->psrc_flag, flag.size()) != hipSuccess)
+        return LBEM_ENOMEM;
+    if (hipMemcpy(h->psrc_idx, idx.data(), idx.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(h->psrc_val, val.data(), val.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(h->psrc_flag, flag.data(), flag.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return LBEM_EDEVICE;
+    h->psrc_pair = pp;
     return LBEM_OK;
 }
 
@@ -1019,10 +1120,10 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
     }
     if (fused_format(h) && h->fuse_ns > 1) {
         int rc;
-        if (D == 2) {
+        if (D == 2 || is_dev(h->prec)) {
             std::vector<std::pair<int64_t, double>> cv(merged.size());
             for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
-            rc = build_march_source(h, cv);
+            rc = D == 2 ? build_march_source(h, cv) : build_pair_source(h, cv, pp);
         } else {
             std::vector<double> dense((size_t)n, 0.0);
             for (size_t k = 0; k < merged.size(); ++k) dense[(size_t)merged[k].first] = src_value[k];

@@ -170,7 +170,7 @@ struct MarchDev {
         const float Lam[1] = {m[0]}, Bb[2] = {m[1], m[2]};
         auto get = [&](int sl) { return h2f<H>(code[sl]); };
 #pragma unroll
-        for (int i = 0; i < 5; ++i) o[i] = dev_eq<2>(i, 0, Lam, Bb, wc0) + dev_value_of<2, GH>(get, i, 0, s, wc0);
+        for (int i = 0; i < 5; ++i) o[i] = dev_pop<2, GH>(get, i, 0, Lam, Bb, s, wc0);
     }
     __device__ __forceinline__ void decode(const Raw& r, const float (&wc0)[CPL], float (&o)[5][CPL]) const
     {
