@@ -161,6 +161,7 @@ struct lbem_s {
     // 3D 16-bit formats: two steps per launch (k_pair_dev3) and its source
     // segments
     PairGeo pgeo;
+    PairGeo ftgeo;       // tiles of the field reader (k_fields_dev3), no blocks: the per-cell reader
     unsigned char* psrc_flag;
     int* psrc_idx;
     float* psrc_val;
@@ -717,6 +718,15 @@ struct DevImpl : Impl {
             return launch_fields<D, float>(h, DevReader<D, H, GH, R_LOCAL>{M(h, h->cur), Dv(h, h->cur), h->n,
                                                                             ext_of(h)},
                                            E, B, partials);
+        if constexpr (D == 3) {
+            // fields alone: tiles that decode each cell once (the diagnostics'
+            // partial sums keep the per-cell kernel's order)
+            if (!partials && h->ftgeo.nblocks && !ext_of(h).walls()) {
+                hipLaunchKernelGGL((k_fields_dev3<H, GH>), dim3(h->ftgeo.nblocks), dim3(1024), 0, h->stream,
+                                   M(h, h->cur), Dv(h, h->cur), (const float*)h->cl2, h->ftgeo, E, B);
+                return hipGetLastError();
+            }
+        }
         return launch_fields<D, float>(h, DevReader<D, H, GH, R_PULL>{M(h, h->cur), Dv(h, h->cur), h->n,
                                                                        ext_of(h)}, E,
                                        B, partials);

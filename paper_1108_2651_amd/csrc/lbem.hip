@@ -85,6 +85,22 @@ static int device_cus()
     return 256;
 }
 
+// The planes per chunk with the least work for tiles that hold a CU each and
+// march along z: rounds of resident blocks times the planes of a chunk, `fill`
+// of which only fill the pipeline.
+static int march_planes(int64_t cols, int nz, int64_t cus, int fill)
+{
+    int64_t best = -1;
+    int lz_best = nz;
+    for (int c = 1; c <= nz; ++c) {
+        const int lz = (nz + c - 1) / c, chunks = (nz + lz - 1) / lz;
+        const int64_t cost = (cols * chunks + cus - 1) / cus * (lz + fill);
+        if (best < 0 || cost < best) { best = cost; lz_best = lz; }
+        if (lz <= 4) break;
+    }
+    return lz_best;
+}
+
 // Two steps per launch for the 3D 16-bit formats (k_pair_dev3): tiles of 60 x
 // 12 stored cells, one block per CU, chunks of lz planes.
 static void make_pair_geo(lbem_s* h)
@@ -93,17 +109,8 @@ static void make_pair_geo(lbem_s* h)
     g.nx = (int)h->cfg.nx; g.ny = (int)h->cfg.ny; g.nz = (int)h->cfg.nz; g.n = h->n;
     g.tiles_x = (g.nx + PRX - 1) / PRX;
     g.tiles_y = (g.ny + PRY - 1) / PRY;
-    // The chunk length with the least work: rounds of resident blocks times the
-    // planes of a chunk, four of which only fill the pipeline.
     const int64_t cus = device_cus(), cols = (int64_t)g.tiles_x * g.tiles_y;
-    int64_t best = -1;
-    for (int c = 1; c <= g.nz; ++c) {
-        const int lz = (g.nz + c - 1) / c, chunks = (g.nz + lz - 1) / lz;
-        const int64_t cost = (cols * chunks + cus - 1) / cus * (lz + 4);
-        if (best < 0 || cost < best) { best = cost; g.lz = lz; }
-        if (lz <= 4) break;
-    }
-    g.lz = std::max(1, env_int("LBEM_FUSE3_LZ", g.lz));
+    g.lz = std::max(1, env_int("LBEM_FUSE3_LZ", march_planes(cols, g.nz, cus, 4)));
     g.nblocks = (int)(cols * ((g.nz + g.lz - 1) / g.lz));
     g.xcd = env_int("LBEM_FUSE3_XCD", std::max(2, g.tiles_x));
     // Taken where enough of the work is on stored cells: n over (rounds * CUs *
@@ -120,6 +127,18 @@ static void make_pair_geo(lbem_s* h)
     const bool ghost = h->prec == LBEM_F16GHOST || h->prec == LBEM_BF16GHOST;
     const double need = (ghost ? 0.28 : 0.36) + (g.nx % 64 == 0 ? 0.09 : 0.0);
     h->fuse_ns = env_int("LBEM_DEV3F", share >= need) ? 2 : 1;
+    // The field reader on tiles of 62 x 14 cells, by the same measure: us per
+    // call, per-cell / tiles: 64^3 (share 0.18) 24.6 / 27.4, 20x200x200 (0.24)
+    // 52.7 / 62.2, 61x100x100 (0.28) 41.9 / 31.2, 80^3 (0.31) 39.3 / 28.9, 128^3
+    // 86.9 / 58.7, 256^3 792 / 491, 250x190x171 437 / 252 (FP16 ghost; all
+    // deviations 0.17 less of a gain).
+    PairGeo& f = h->ftgeo;
+    f = g;
+    f.tiles_x = (f.nx + FLX - 1) / FLX;
+    f.tiles_y = (f.ny + FLY - 1) / FLY;
+    f.lz = march_planes((int64_t)f.tiles_x * f.tiles_y, f.nz, cus, 2);
+    f.xcd = std::max(2, f.tiles_x);
+    f.nblocks = env_int("LBEM_FIELDS3", share >= 0.27) ? f.tiles_x * f.tiles_y * ((f.nz + f.lz - 1) / f.lz) : 0;
 }
 
 static void make_fused_geo(lbem_s* h)

@@ -250,4 +250,112 @@ __global__ __launch_bounds__(1024, 4) void k_pair_dev3(const float* Min, const H
                                      zc * g.lz, ly);
 }
 
+// E and B of a 3D 16-bit state not yet streamed, on the tiles of the march
+// above with one level: every stored cell is decoded once (the per-cell reader
+// decodes each arrival from its neighbour's moments and codes), 62 x 14 cells
+// of a tile are written.  Same arithmetic as k_fields, so the same bits.
+// Bound by memory, 58 B read and 48 B written per cell (FP16 ghost): 256^3 792
+// -> 491 us per call (3.6 TB/s), 512^3 6.4 -> 3.6 ms.
+constexpr int FLX = 62, FLY = 14;
+
+template <typename H, bool GH>
+__global__ __launch_bounds__(1024, 4) void k_fields_dev3(const float* Min, const H* Din, const float* cl2a,
+                                                        const PairGeo g, double* E, double* B)
+{
+    constexpr int D = 3, Q = 7, P = 3, NM = 6, NC = DevSlots<D, GH>::N;
+    __shared__ float ly[2][2 * P][1024];  // [buffer][+y 0..2, -y 3..5][row * 64 + lane]
+    const int b = remap_block(blockIdx.x, g.nblocks, g.xcd);
+    const int tx = b % g.tiles_x, r = b / g.tiles_x;
+    const int ty = r % g.tiles_y, zc = r / g.tiles_y;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int tid = threadIdx.x;
+    const int x0 = tx * FLX, y0 = ty * FLY, z0 = zc * g.lz;
+    const int planes = min(g.lz, g.nz - z0);
+    auto wrap = [](int v, int m) { v %= m; return v < 0 ? v + m : v; };
+    const unsigned col0 = (unsigned)wrap(x0 - 1 + lane, g.nx);
+    const int64_t nxy = (int64_t)g.nx * g.ny, rowo = (int64_t)wrap(y0 - 1 + w, g.ny) * g.nx;
+    const bool edge = w == 0 || w == 15;               // rows decoded for their +y / -y populations only
+    const bool keep = !edge && lane >= 1 && lane < 1 + FLX && x0 - 1 + lane < g.nx && y0 - 1 + w < g.ny;
+
+    float m[NM], cl = 1.f;
+    H cd[NC] = {};
+    int gz = wrap(z0 - 1, g.nz);
+    auto fetch = [&]() {
+        const int64_t o = (int64_t)gz * nxy + rowo;
+        unsigned col = col0;
+        asm volatile("" : "+v"(col));
+#pragma unroll
+        for (int t = 0; t < NM; ++t) m[t] = at32(Min + (int64_t)t * g.n + o, col);
+#pragma unroll
+        for (int s = 0; s < NC; ++s)
+            if (pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
+        if (!edge) {
+#pragma unroll
+            for (int s = 0; s < NC; ++s)
+                if (!pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
+            cl = at32(cl2a + o, col);
+        }
+        gz = gz + 1 == g.nz ? 0 : gz + 1;
+    };
+    float rest[P] = {}, px[P] = {}, mx[P] = {}, pz[P] = {}, pzo[P] = {}, clp = 1.f;   // of the plane before
+    fetch();
+    for (int it = 0; it < planes + 2; ++it) {
+        const int bw = it & 1, br = bw ^ 1;
+        const float wc0 = 1.f / cl - float(D), sc = row_scale(m), cl0 = cl;
+        float cf[NC], nrest[P], npx[P], nmx[P], npz[P], mz[P];
+#pragma unroll
+        for (int s = 0; s < NC; ++s) cf[s] = h2f<H>(cd[s]);
+        auto get = [&](int s) { return cf[s]; };
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            ly[bw][p][tid] = row_pop<GH>(m, get, sc, wc0, 2, p);
+            ly[bw][P + p][tid] = row_pop<GH>(m, get, sc, wc0, 5, p);
+            nrest[p] = row_pop<GH>(m, get, sc, wc0, 0, p);
+            npx[p] = row_pop<GH>(m, get, sc, wc0, 1, p);
+            nmx[p] = row_pop<GH>(m, get, sc, wc0, 4, p);
+            npz[p] = row_pop<GH>(m, get, sc, wc0, 3, p);
+            mz[p] = row_pop<GH>(m, get, sc, wc0, 6, p);
+        }
+        if (it + 1 < planes + 2) fetch();
+        if (it >= 2 && !edge) {
+            double f[Q][P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                f[0][p] = (double)rest[p];
+                f[1][p] = (double)lane_shift<1>(px[p]);
+                f[2][p] = (double)ly[br][p][tid - 64];
+                f[3][p] = (double)pzo[p];
+                f[4][p] = (double)lane_shift<-1>(mx[p]);
+                f[5][p] = (double)ly[br][P + p][tid + 64];
+                f[6][p] = (double)mz[p];
+            }
+            double rho[P], K[D];
+            moments<D, double>(f, rho, K);
+            const int64_t o = (int64_t)(z0 + it - 2) * nxy + rowo;
+            if (keep) {
+                const double cld = (double)clp;
+                if (E) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p)
+                        at32(E + (int64_t)pair_g(D, p) * g.n + o, col0) = -(double)pair_s(D, p) * (cld * rho[p]);
+                }
+                if (B) {
+#pragma unroll
+                    for (int k = 0; k < D; ++k) at32(B + (int64_t)k * g.n + o, col0) = K[k];
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            rest[p] = nrest[p];
+            px[p] = npx[p];
+            mx[p] = nmx[p];
+            pzo[p] = pz[p];
+            pz[p] = npz[p];
+        }
+        clp = cl0;
+        __syncthreads();
+    }
+}
+
 }  // namespace lbem

@@ -29,6 +29,26 @@ def test_tile_and_chunk_edges(shape, mu):
                 got.close()
 
 
+@pytest.mark.parametrize("shape", [(62, 14, 6), (63, 15, 7), (61, 13, 5), (3, 4, 5), (130, 30, 1)])
+def test_fields_on_tiles(shape):
+    """E and B read on tiles (62 x 14 cells, each stored cell decoded once)
+    equal the per-cell reader's, both fields together and each alone."""
+    import torch
+    p = random_problem(3, shape, seed=sum(shape), nsteps=3)
+    for prec in ("f16dev", "f16ghost", "bf16dev", "bf16ghost"):
+        announce(f"fields on tiles {prec} {shape}")
+        a = gpu_run(p, 3, prec, "pull", env={"LBEM_FIELDS3": 0})
+        b = gpu_run(p, 3, prec, "pull", env={"LBEM_FIELDS3": 1})
+        (Ea, Ba), (Eb, Bb) = a.moments(), b.moments()
+        assert np.array_equal(Ea, Eb) and np.array_equal(Ba, Bb), (prec, shape)
+        E = torch.zeros((3, p.n), dtype=torch.float64, device="cuda")
+        B = torch.zeros_like(E)
+        b.moments_device(E, B)
+        assert np.array_equal(E.cpu().numpy(), Ea) and np.array_equal(B.cpu().numpy(), Ba)
+        a.close()
+        b.close()
+
+
 def test_default_takes_the_pair_on_large_boxes():
     """From about 88^3 on; the default equals single steps."""
     p = random_problem(3, (101, 96, 90), seed=3, nsteps=5)
