@@ -461,7 +461,17 @@ int lbem_create(const lbem_config* cfg, lbem_t* out)
     {
         const double touched = (double)s.pop_one * (h->streaming == LBEM_STREAM_AA ? 1 : 2);
         const double lim = (double)env_int("LBEM_NT_MIB", h->D == 2 ? 256 : 384) * (1 << 20);
-        h->nts = env_int("LBEM_NT", touched > lim ? 1 : 0) != 0;
+        // In 3D only where rows end on the boundaries that the store path
+        // combines within: streamed partial lines leave the caches before the
+        // neighbouring row or tile completes them.  Measured, us per step,
+        // streaming / plain: FP32 pair 256^3 303 / 317, nx = 248 250 / 232, 252
+        // 288 / 251, 257 346 / 272; FP64 AA 248 694 / 729, 252 772 / 739 (FP64
+        // pull with a pole 1025 / 1061, so pull keeps streaming); FP16 ghost row
+        // tiles with walls 248 252 / 267, 252 290 / 276, 257 406 / 299.
+        const int64_t row = cfg->nx * (cfg->prec == LBEM_F64 ? 8 : (cfg->prec == LBEM_F16 ? 2 : 4));
+        const bool whole = h->D == 2 || (is_dev(cfg->prec) ? cfg->nx % 8 == 0 : row % 64 == 0) ||
+                           (cfg->prec == LBEM_F64 && h->streaming != LBEM_STREAM_AA);
+        h->nts = env_int("LBEM_NT", touched > lim && whole ? 1 : 0) != 0;
     }
     h->impl = make_impl(h->D, h->prec);
     if (h->impl && (hipEventCreateWithFlags(&h->sync_ev, hipEventDisableTiming) != hipSuccess ||
