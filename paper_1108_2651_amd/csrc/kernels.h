@@ -1757,6 +1757,27 @@ __global__ __launch_bounds__(NTB, (EXT != 0 && !GH) ? 3 : 4) void k_step_dev3r(c
 // ---------------------------------------------------------------------------
 // batched persistent stream-collide: many independent lattices per launch
 // ---------------------------------------------------------------------------
+// Columns recomputed at each end of a 2D strip (march2d.h), the same for every
+// number of steps, so that one source table serves them all.
+constexpr int MARCH_HX = 4;
+
+struct MarchGeo {
+    int nx, ny;
+    int strips;          // column strips of 64*CPL - 2*MARCH_HX stored columns
+    int rows;            // rows per chunk, at most 64 - 2*MARCH_HX
+    int nwork;           // strips * chunks
+    int nblocks;         // a multiple of 8: each XCD takes one contiguous range of work items
+    int64_t n;
+};
+
+// Tiles of the 3D two-step kernel (pair3d.h).
+struct PairGeo {
+    int nx, ny, nz;
+    int tiles_x, tiles_y, lz;            // planes per chunk
+    int nblocks, xcd;
+    int64_t n;
+};
+
 // One descriptor per resident lattice.  Work items are (lattice, tile) pairs
 // numbered by the prefix tile_base; a persistent grid strides over them.  The
 // per-cell code is the same inline code as the single-lattice kernels, so a
@@ -1789,6 +1810,17 @@ struct BatchGrid {
     const int* rsrc_off;
     const int2* rsrc_ent;
     const float* rsrc_val;
+    // multi-step launches (16-bit formats): the tiling of this group and the
+    // handle's source segments
+    int multi_base;
+    MarchGeo mgeo;       // 2D
+    const int* msrc_idx;
+    const float* msrc_val;
+    unsigned msrc_mask[8];
+    PairGeo pgeo;        // 3D
+    const int* psrc_idx;
+    const float* psrc_val;
+    int psrc_pair;
 };
 
 // A pointer read from the descriptor table, as a global-memory pointer.  The
@@ -1808,16 +1840,17 @@ struct BatchHdr {
     int count;           // lattices in the table
     int total_tiles;     // work items of the per-cell tiles
     int total_rows;      // work items of the whole-row tiles (all members row)
+    int total_multi;     // work items of the multi-step kernels (waves in 2D, blocks in 3D)
 };
 
-// the member that owns work item w (ROWS: of the whole-row numbering)
-template <bool ROWS = false>
+// the member that owns work item w of the numbering BASE
+template <int BatchGrid::*BASE = &BatchGrid::tile_base>
 __device__ __forceinline__ int batch_find(const BatchGrid* __restrict__ tab, int count, int w)
 {
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if ((ROWS ? tab[mid].row_base : tab[mid].tile_base) <= w) lo = mid;
+        if (tab[mid].*BASE <= w) lo = mid;
         else hi = mid - 1;
     }
     return lo;
@@ -1880,8 +1913,9 @@ __device__ __forceinline__ void batch_tile_plain(const BatchGrid& G, int tile, i
             dst[(int64_t)(write_slot<D, WM>(i) * P + p) * g.n + write_cell<D, WM>(C, i)] = st_pop<S>(out[i][p]);
 }
 
+// step k of the tick, reading copy cur0 + flips
 template <int D, typename H, bool GH, int RM>
-__device__ __forceinline__ void batch_tile_dev(const BatchGrid& G, int tile, int k, float* lds)
+__device__ __forceinline__ void batch_tile_dev(const BatchGrid& G, int tile, int k, int flips, float* lds)
 {
     constexpr int Q = Lat<D>::Q, P = Lat<D>::P;
     const Geo& g = G.geo;
@@ -1893,7 +1927,7 @@ __device__ __forceinline__ void batch_tile_dev(const BatchGrid& G, int tile, int
     const bool has_src = batch_source<P, float>(G, tile, k, lds);
     const bool mu = G.dlnmu != nullptr;
     if (x >= g.nx || y >= g.ny) return;
-    const int s = (G.cur0 + k) & 1;
+    const int s = (G.cur0 + flips) & 1;
     const float* Min = gmem<const float>(G.buf[s]);
     const H* Din = gmem<const H>(G.dev[s]);
     float* Mout = gmem<float>(G.buf[s ^ 1]);
@@ -1945,18 +1979,28 @@ __global__ __launch_bounds__(NT) void k_step_batch_plain(const BatchHdr* __restr
     }
 }
 
+// multi = 0: step k of the tick.  multi = m: the tick runs one step, then
+// launches of m steps, and this is single step k < (nsteps - 1) % m after them.
 template <int D, typename H, bool GH>
 __global__ __launch_bounds__(NT) void k_step_batch_dev(const BatchHdr* __restrict__ hdr,
-                                                      const BatchGrid* __restrict__ tab, int k)
+                                                      const BatchGrid* __restrict__ tab, int k, int multi)
 {
     __shared__ float lds[Lat<D>::P * NT];
     const int count = hdr->count, total = hdr->total_tiles;
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
         const int gi = batch_find(tab, count, w);
         const BatchGrid& G = tab[gi];
-        if (k >= G.nsteps) continue;
-        if (G.fresh && k == 0) batch_tile_dev<D, H, GH, R_LOCAL>(G, w - G.tile_base, k, lds);
-        else batch_tile_dev<D, H, GH, R_PULL>(G, w - G.tile_base, k, lds);
+        int step = k, flips = k;
+        if (multi) {
+            const int rest = G.nsteps > 0 ? (G.nsteps - 1) % multi : 0;
+            if (k >= rest) continue;
+            step = G.nsteps - rest + k;
+            flips = 1 + (G.nsteps - 1) / multi + k;
+        } else if (k >= G.nsteps) {
+            continue;
+        }
+        if (G.fresh && step == 0) batch_tile_dev<D, H, GH, R_LOCAL>(G, w - G.tile_base, step, flips, lds);
+        else batch_tile_dev<D, H, GH, R_PULL>(G, w - G.tile_base, step, flips, lds);
         __syncthreads();   // the next work item may stage its source into lds
     }
 }
@@ -1979,7 +2023,7 @@ __global__ __launch_bounds__(BROW_NT, 4) void k_step_batch_dev3_rows(const Batch
     __shared__ float lds[L::FLOATS];
     const int count = hdr->count, total = hdr->total_rows;
     for (int w = blockIdx.x; w < total; w += gridDim.x) {
-        const int gi = batch_find<true>(tab, count, w);
+        const int gi = batch_find<&BatchGrid::row_base>(tab, count, w);
         const BatchGrid& G = tab[gi];
         if (k >= G.nsteps) continue;
         const int s = (G.cur0 + k) & 1;

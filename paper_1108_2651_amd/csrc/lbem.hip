@@ -1,6 +1,7 @@
 // lbem.hip -- host side of liblbem: the C ABI declared in include/lbem.h,
 // device memory, tilings, source tables and batched stepping.
 #include "impl.h"
+#include "batch_multi.h"
 
 namespace {
 // Graph capture of the batched kernels (lbem_batch_create) holds this lock
@@ -1394,6 +1395,7 @@ struct lbem_batch_s {
     int use_graph;
     int blocks;                // persistent grid of each class launch
     int rows_min;              // fewest whole-row work items for the row modes
+    int multi;                 // several steps per launch for the 16-bit classes: 0 never, 1 by size, 2 always
     // the classes of a tick run concurrently, one stream each (default
     // priority), forked from the batch stream after the table upload and
     // joined back before anything later on it
@@ -1406,7 +1408,7 @@ struct lbem_batch_s {
 // members that start from the natural layout
 template <int D, typename H, bool GH>
 static void launch_batch_dev(dim3 g, dim3 t, hipStream_t st, const BatchHdr* hdr, const BatchGrid* tab, int k,
-                             int mode)
+                             int mode, int multi)
 {
     if constexpr (D == 3) {
         if (k > 0 && mode == MODE_ROWS) {
@@ -1418,38 +1420,84 @@ static void launch_batch_dev(dim3 g, dim3 t, hipStream_t st, const BatchHdr* hdr
             return;
         }
     }
-    hipLaunchKernelGGL((k_step_batch_dev<D, H, GH>), g, t, 0, st, hdr, tab, k);
+    hipLaunchKernelGGL((k_step_batch_dev<D, H, GH>), g, t, 0, st, hdr, tab, k, multi);
 }
 
 template <int D>
 static void launch_class_d(lbem_batch_s* b, int prec, const BatchHdr* hdr, const BatchGrid* tab, int k,
-                           hipStream_t st, int mode)
+                           hipStream_t st, int mode, int multi)
 {
     dim3 g(b->blocks), t(NT);
     switch (prec) {
         case LBEM_F64: hipLaunchKernelGGL((k_step_batch_plain<D, double>), g, t, 0, st, hdr, tab, k); break;
         case LBEM_F32: hipLaunchKernelGGL((k_step_batch_plain<D, float>), g, t, 0, st, hdr, tab, k); break;
-        case LBEM_F16DEV: launch_batch_dev<D, __half, false>(g, t, st, hdr, tab, k, mode); break;
-        case LBEM_BF16DEV: launch_batch_dev<D, __hip_bfloat16, false>(g, t, st, hdr, tab, k, mode); break;
-        case LBEM_F16GHOST: launch_batch_dev<D, __half, true>(g, t, st, hdr, tab, k, mode); break;
-        case LBEM_BF16GHOST: launch_batch_dev<D, __hip_bfloat16, true>(g, t, st, hdr, tab, k, mode); break;
+        case LBEM_F16DEV: launch_batch_dev<D, __half, false>(g, t, st, hdr, tab, k, mode, multi); break;
+        case LBEM_BF16DEV: launch_batch_dev<D, __hip_bfloat16, false>(g, t, st, hdr, tab, k, mode, multi); break;
+        case LBEM_F16GHOST: launch_batch_dev<D, __half, true>(g, t, st, hdr, tab, k, mode, multi); break;
+        case LBEM_BF16GHOST: launch_batch_dev<D, __hip_bfloat16, true>(g, t, st, hdr, tab, k, mode, multi); break;
         default:
             hipLaunchKernelGGL((k_step_batch_plain<D, float, __half>), g, t, 0, st, hdr, tab, k);
             break;
     }
 }
 
-static void launch_class(lbem_batch_s* b, int c, int k, hipStream_t st, int mode)
+// launch k of a class; multi = m > 0: single step k after launches of m steps
+static void launch_class(lbem_batch_s* b, int c, int k, hipStream_t st, int mode, int multi = 0)
 {
     const size_t cb = class_bytes(b->max_grids);
     const BatchHdr* hdr = (const BatchHdr*)(b->dev + c * cb);
     const BatchGrid* tab = (const BatchGrid*)(b->dev + c * cb + align256(sizeof(BatchHdr)));
-    if (c < NPREC) launch_class_d<2>(b, c, hdr, tab, k, st, mode);
-    else launch_class_d<3>(b, c - NPREC, hdr, tab, k, st, mode);
+    if (c < NPREC) launch_class_d<2>(b, c, hdr, tab, k, st, mode, multi);
+    else launch_class_d<3>(b, c - NPREC, hdr, tab, k, st, mode, multi);
 }
 
 // classes that have the row modes: 3D deviation formats
 static bool has_row_modes(int c) { return c >= NPREC && is_dev(c - NPREC); }
+
+// A class's tick with several steps per launch (16-bit formats): one single
+// step, `launches` launches of m steps on `blocks` blocks, `rest` single steps.
+struct MultiPlan {
+    int m;               // 0: the class runs one step per launch
+    int launches, rest, blocks;
+    bool mu;
+};
+
+template <typename H, bool GH>
+static void launch_multi_f(int D, const MultiPlan& p, hipStream_t st, const BatchHdr* hdr, const BatchGrid* tab, int j)
+{
+    const dim3 g(p.blocks);
+    if (D == 2) {
+        if (p.mu) hipLaunchKernelGGL((k_batch_march2d<H, GH, true>), g, dim3(NT), 0, st, hdr, tab, j);
+        else hipLaunchKernelGGL((k_batch_march2d<H, GH, false>), g, dim3(NT), 0, st, hdr, tab, j);
+    } else {
+        if (p.mu) hipLaunchKernelGGL((k_batch_pair3d<H, GH, true>), g, dim3(1024), 0, st, hdr, tab, j);
+        else hipLaunchKernelGGL((k_batch_pair3d<H, GH, false>), g, dim3(1024), 0, st, hdr, tab, j);
+    }
+}
+
+// the launches of a class on a multi-step plan, directly on the stream: a
+// quarter or half as many as steps, so they need no graph
+static hipError_t launch_multi(lbem_batch_s* b, int c, const MultiPlan& p, hipStream_t st)
+{
+    const size_t cb = class_bytes(b->max_grids);
+    const BatchHdr* hdr = (const BatchHdr*)(b->dev + c * cb);
+    const BatchGrid* tab = (const BatchGrid*)(b->dev + c * cb + align256(sizeof(BatchHdr)));
+    const int D = c < NPREC ? 2 : 3, prec = c < NPREC ? c : c - NPREC;
+    launch_class(b, c, 0, st, MODE_CELL);
+    for (int j = 0; j < p.launches; ++j) {
+        switch (prec) {
+            case LBEM_F16DEV: launch_multi_f<__half, false>(D, p, st, hdr, tab, j); break;
+            case LBEM_BF16DEV: launch_multi_f<__hip_bfloat16, false>(D, p, st, hdr, tab, j); break;
+            case LBEM_F16GHOST: launch_multi_f<__half, true>(D, p, st, hdr, tab, j); break;
+            default: launch_multi_f<__hip_bfloat16, true>(D, p, st, hdr, tab, j); break;
+        }
+    }
+    for (int k = 0; k < p.rest; ++k) launch_class(b, c, k, st, MODE_CELL, p.m);
+    return hipGetLastError();
+}
+
+// The launches a member takes part in: the copy that holds its state flips in each.
+static int multi_flips(int64_t nsteps, int m) { return (int)(1 + (nsteps - 1) / m + (nsteps - 1) % m); }
 
 // Capture the per-class graphs.  Done once, at creation, with the library
 // lock held exclusively: no graph is ever captured or instantiated while
@@ -1479,7 +1527,7 @@ static bool capture_classes(lbem_batch_s* b)
     return true;
 }
 
-static hipError_t enqueue_tick(lbem_batch_s* b, unsigned mask, const int* mode)
+static hipError_t enqueue_tick(lbem_batch_s* b, unsigned mask, const int* mode, const MultiPlan* plan)
 {
     const bool conc = b->concurrent && (mask & (mask - 1)) != 0;   // two classes or more
     hipError_t e = hipSuccess;
@@ -1491,7 +1539,9 @@ static hipError_t enqueue_tick(lbem_batch_s* b, unsigned mask, const int* mode)
             st = b->cstream[c];
             if ((e = hipStreamWaitEvent(st, b->fork_ev, 0)) != hipSuccess) return e;
         }
-        if (b->use_graph) {
+        if (plan[c].m) {
+            if ((e = launch_multi(b, c, plan[c], st)) != hipSuccess) return e;
+        } else if (b->use_graph) {
             if ((e = hipGraphLaunch(b->exec[c][mode[c]], st)) != hipSuccess) return e;
         } else {
             for (int k = 0; k < b->ksteps; ++k) launch_class(b, c, k, st, mode[c]);
@@ -1524,10 +1574,93 @@ static size_t touched_bytes(const lbem_s* h)
     return z.pop_one * (h->streaming == LBEM_STREAM_AA ? 1 : 2) + z.medium + (h->mu_set ? z.mu : 0);
 }
 
+// Whether class c's members of a group (its cnt entries of the table, in the
+// order of idx) take several steps per launch, and if so their tilings.  The
+// rows or planes per chunk are chosen for the members together, as the solo
+// tilings choose them for one lattice.
+static MultiPlan plan_multi(const lbem_batch_s* b, int c, char* host, const lbem_t* handles, const int64_t* nsteps,
+                            const int* idx, int m, int cnt, int nmu)
+{
+    MultiPlan p{};
+    const int prec = c < NPREC ? c : c - NPREC, D = c < NPREC ? 2 : 3;
+    if (!b->multi || cnt == 0 || !is_dev(prec) || (nmu != 0 && nmu != cnt)) return p;
+    const size_t cb = class_bytes(b->max_grids);
+    BatchGrid* tab = (BatchGrid*)(host + c * cb + align256(sizeof(BatchHdr)));
+    BatchHdr* hd = (BatchHdr*)(host + c * cb);
+    const int ms = D == 2 ? 4 : 2;
+    int64_t longest = 0, rows = 0, cells = 0;
+    bool lines = true;                         // rows of whole 64-cell lines in every member
+    std::vector<const lbem_s*> mem;
+    for (int q = 0; q < m; ++q) {
+        const lbem_s* h = handles[idx[q]];
+        if (class_of(h) != c) continue;
+        // a source needs its segments (a 3D handle below the solo kernel's size
+        // rule has none)
+        if (h->nsrc && !(D == 2 ? h->nmsrc > 0 : h->psrc_idx != nullptr)) return p;
+        mem.push_back(h);
+        longest = std::max(longest, nsteps[idx[q]]);
+        p.rest = std::max(p.rest, (int)((nsteps[idx[q]] - 1) % ms));
+        rows += (int64_t)h->mgeo.strips * h->cfg.ny;
+        cells += h->n;
+        lines = lines && h->cfg.nx % 64 == 0;
+    }
+    p.launches = (int)((longest - 1) / ms);
+    if (p.launches < 1) return MultiPlan{};
+    int64_t total = 0;
+    if (D == 2) {
+        const int64_t slots = 4096, rounds = ((rows + slots - 1) / slots + 23) / 24, per = std::max<int64_t>(1, rounds) * slots;
+        const int r = (int)std::max<int64_t>(2, (rows + per - 1) / per);
+        for (int k = 0; k < cnt; ++k) {
+            MarchGeo& g = tab[k].mgeo;
+            g = mem[k]->mgeo;
+            g.rows = std::min(r, g.ny);
+            g.nwork = g.strips * ((g.ny + g.rows - 1) / g.rows);
+            tab[k].msrc_idx = mem[k]->msrc_idx;
+            tab[k].msrc_val = (const float*)mem[k]->msrc_val;
+            for (int w = 0; w < 8; ++w) tab[k].msrc_mask[w] = mem[k]->nmsrc ? mem[k]->msrc_mask[w] : 0u;
+            tab[k].multi_base = (int)total;
+            total += g.nwork;
+        }
+        p.blocks = (int)((total + NT / 64 - 1) / (NT / 64));
+    } else {
+        const int64_t cus = device_cus();
+        int64_t best = -1;
+        int lz = 4, longest_z = 1;
+        for (const lbem_s* h : mem) longest_z = std::max(longest_z, (int)h->cfg.nz);
+        for (int z = std::min(4, longest_z); z <= longest_z; ++z) {
+            int64_t nb = 0;
+            for (const lbem_s* h : mem) nb += (int64_t)h->pgeo.tiles_x * h->pgeo.tiles_y * ((h->cfg.nz + z - 1) / z);
+            const int64_t cost = (nb + cus - 1) / cus * (z + 4);
+            if (best < 0 || cost < best) { best = cost; lz = z; }
+        }
+        // the share of the work that is on stored cells, as for a single lattice
+        const bool ghost = prec == LBEM_F16GHOST || prec == LBEM_BF16GHOST;
+        const double share = (double)cells / ((double)best * cus * (PRX * PRY));
+        if (b->multi < 2 && share < (ghost ? 0.28 : 0.36) + (lines ? 0.09 : 0.0)) return MultiPlan{};
+        for (int k = 0; k < cnt; ++k) {
+            PairGeo& g = tab[k].pgeo;
+            g = mem[k]->pgeo;
+            g.lz = std::min(lz, g.nz);
+            g.nblocks = g.tiles_x * g.tiles_y * ((g.nz + g.lz - 1) / g.lz);
+            tab[k].psrc_idx = mem[k]->psrc_idx;
+            tab[k].psrc_val = mem[k]->psrc_val;
+            tab[k].psrc_pair = mem[k]->psrc_pair;
+            tab[k].multi_base = (int)total;
+            total += g.nblocks;
+        }
+        p.blocks = (int)total;
+    }
+    hd->total_multi = (int)total;
+    p.m = ms;
+    p.mu = nmu != 0;
+    return p;
+}
+
 // One group of a tick: its descriptor table through the next staging slot,
 // the ordering against the members' own streams, and the classes' graphs.
+// flips[i]: how often member i's state changes copies.
 static int enqueue_group(lbem_batch_s* b, const lbem_t* handles, const int64_t* nsteps, const double* amp,
-                         const int* idx, int m)
+                         const int* idx, int m, int* flips)
 {
     // the staging slot is free once its previous upload has executed
     if (hipEventSynchronize(b->ev[b->ring]) != hipSuccess) return LBEM_EDEVICE;
@@ -1601,6 +1734,12 @@ static int enqueue_group(lbem_batch_s* b, const lbem_t* handles, const int64_t* 
         tiles[c] += g.nblocks;
         mask |= 1u << c;
     }
+    MultiPlan plan[NCLASS];
+    for (int c = 0; c < NCLASS; ++c) plan[c] = plan_multi(b, c, host, handles, nsteps, idx, m, cnt[c], nmu[c]);
+    for (int q = 0; q < m; ++q) {
+        const MultiPlan& p = plan[class_of(handles[idx[q]])];
+        flips[idx[q]] = p.m ? multi_flips(nsteps[idx[q]], p.m) : (int)nsteps[idx[q]];
+    }
     int mode[NCLASS];
     for (int c = 0; c < NCLASS; ++c) {
         BatchHdr* hd = (BatchHdr*)(host + c * cb);
@@ -1626,7 +1765,7 @@ static int enqueue_group(lbem_batch_s* b, const lbem_t* handles, const int64_t* 
         return LBEM_EDEVICE;
     if (hipEventRecord(b->ev[b->ring], b->stream) != hipSuccess) return LBEM_EDEVICE;
     b->ring = (b->ring + 1) % NRING;
-    if (mask && enqueue_tick(b, mask, mode) != hipSuccess) return LBEM_EDEVICE;
+    if (mask && enqueue_tick(b, mask, mode, plan) != hipSuccess) return LBEM_EDEVICE;
     // ... and later work on a member's own stream (moments, destroy) follows
     // it: the member's stream waits on this event at its next use (follow_ticks)
     for (int q = 0; q < m; ++q) {
@@ -1662,6 +1801,7 @@ int lbem_batch_create(int max_lattices, int steps_per_tick, void* stream, lbem_b
     // tiles always on (100 req/s: p50 141 against 62 ms).  So a class takes
     // them only with enough items to fill the GPU several times over.
     b->rows_min = std::max(0, env_int("LBEM_BATCH_ROWS_MIN", 1536));
+    b->multi = env_int("LBEM_BATCH_MULTI", 1);
     b->amp_off = class_bytes(max_lattices) * NCLASS;
     const size_t bytes = b->amp_off + align256((size_t)max_lattices * steps_per_tick * 8);
     b->dev = nullptr;
@@ -1776,6 +1916,7 @@ int lbem_batch_run_amp(lbem_batch_t b, const lbem_t* handles, const int64_t* nst
     if (b->group_bytes)
         std::stable_sort(order.begin(), order.end(),
                          [&](int x, int y) { return class_of(handles[x]) < class_of(handles[y]); });
+    std::vector<int> flips(count, 0);
     size_t g0 = 0;
     while (g0 < order.size()) {
         size_t g1 = g0, used = 0;
@@ -1790,7 +1931,7 @@ int lbem_batch_run_amp(lbem_batch_t b, const lbem_t* handles, const int64_t* nst
             }
             ++g1;
         }
-        const int rc = enqueue_group(b, handles, nsteps, amp, order.data() + g0, (int)(g1 - g0));
+        const int rc = enqueue_group(b, handles, nsteps, amp, order.data() + g0, (int)(g1 - g0), flips.data());
         if (rc != LBEM_OK) return rc;
         g0 = g1;
     }
@@ -1800,7 +1941,7 @@ int lbem_batch_run_amp(lbem_batch_t b, const lbem_t* handles, const int64_t* nst
         if (h->streaming == LBEM_STREAM_AA) {
             if (nsteps[i] & 1) h->layout = h->layout == LAYOUT_NATURAL ? LAYOUT_AA_SWAPPED : LAYOUT_NATURAL;
         } else {
-            if (nsteps[i] & 1) h->cur = 1 - h->cur;
+            if (flips[i] & 1) h->cur = 1 - h->cur;
             h->layout = LAYOUT_PULL_PENDING;
         }
         h->t += nsteps[i];

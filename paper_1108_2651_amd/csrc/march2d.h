@@ -55,19 +55,6 @@ __device__ __forceinline__ T lane_shift(T v)
     }
 }
 
-// Columns recomputed at each end of a strip, the same for every number of
-// steps, so that one source table serves them all.
-constexpr int MARCH_HX = 4;
-
-struct MarchGeo {
-    int nx, ny;
-    int strips;          // column strips of 64*CPL - 2*MARCH_HX stored columns
-    int rows;            // rows per chunk, at most 64 - 2*MARCH_HX
-    int nwork;           // strips * chunks
-    int nblocks;         // a multiple of 8: each XCD takes one contiguous range of work items
-    int64_t n;
-};
-
 // Sparse current source: idx[strip*ny + row] is the segment of that strip's
 // row (64*CPL values, S per unit amplitude, periodic images included) or -1.
 // Bit strip % 256 of mask is set for every strip that holds a source: the
@@ -392,16 +379,14 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
 #undef LBEM_IC
 }
 
+// Work item w (uniform over the wave).
 template <class IO, int NS, int CPL, bool MU, bool TH>
-__global__ __launch_bounds__(NT) void k_march2d(const IO io, const typename IO::T* __restrict__ cl2a,
-                                               const typename IO::T* __restrict__ dlnmu, const MarchGeo g,
-                                               const MarchSrc<typename IO::T> ms,
-                                               const AmpPack<typename IO::T, NS> amps,
-                                               const typename IO::T omega, const int tau_half)
+__device__ __forceinline__ void march2d_work(const IO& io, const typename IO::T* __restrict__ cl2a,
+                                             const typename IO::T* __restrict__ dlnmu, const MarchGeo& g,
+                                             const MarchSrc<typename IO::T>& ms,
+                                             const AmpPack<typename IO::T, NS>& amps,
+                                             const typename IO::T omega, const bool tau_half, const int w)
 {
-    const int b = remap_block(blockIdx.x, g.nblocks, 1);
-    const int w = __builtin_amdgcn_readfirstlane(b * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6));
-    if (w >= g.nwork) return;
     const int strip = w % g.strips, y0 = (w / g.strips) * g.rows;
     unsigned m = 0;
 #pragma unroll
@@ -420,14 +405,24 @@ __global__ __launch_bounds__(NT) void k_march2d(const IO io, const typename IO::
     }
     const bool up = (w / g.strips) & 1;
     if (src)
-        march2d_item<IO, NS, CPL, MU, TH, true, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
-                                                       segs);
+        march2d_item<IO, NS, CPL, MU, TH, true, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
     else if (up)
-        march2d_item<IO, NS, CPL, MU, TH, false, true>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
-                                                       segs);
+        march2d_item<IO, NS, CPL, MU, TH, false, true>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
     else
-        march2d_item<IO, NS, CPL, MU, TH, false, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, strip, y0,
-                                                       segs);
+        march2d_item<IO, NS, CPL, MU, TH, false, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
+}
+
+template <class IO, int NS, int CPL, bool MU, bool TH>
+__global__ __launch_bounds__(NT) void k_march2d(const IO io, const typename IO::T* __restrict__ cl2a,
+                                               const typename IO::T* __restrict__ dlnmu, const MarchGeo g,
+                                               const MarchSrc<typename IO::T> ms,
+                                               const AmpPack<typename IO::T, NS> amps,
+                                               const typename IO::T omega, const int tau_half)
+{
+    const int b = remap_block(blockIdx.x, g.nblocks, 1);
+    const int w = __builtin_amdgcn_readfirstlane(b * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6));
+    if (w >= g.nwork) return;
+    march2d_work<IO, NS, CPL, MU, TH>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, w);
 }
 
 }  // namespace lbem

@@ -46,13 +46,6 @@ __device__ __forceinline__ const T& at32(const T* base, unsigned idx)
 
 constexpr int PRX = 60, PRY = 12;        // stored columns and rows of a tile (64 lanes x 16 waves)
 
-struct PairGeo {
-    int nx, ny, nz;
-    int tiles_x, tiles_y, lz;            // planes per chunk
-    int nblocks, xcd;
-    int64_t n;
-};
-
 struct PairSrc {
     const unsigned char* flag;           // per block: some row it updates holds source cells (nullptr: no source)
     const int* idx;                      // [tile_x][z][y]: segment of the 64 columns of that strip's row, or -1
