@@ -147,11 +147,14 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
  * distrib.func) with the BGK collision and the tensor source (eq. COLLI), and
  * streams (eq. STREAM).  amp (host, nsteps doubles, may be NULL = no
  * source) gives the source amplitude of each step: step k of this call uses
- * amp[k] at time t0 + k.  ESTATE before lbem_init_fields.  Periodic handles in
- * the plain formats with pull streaming advance several steps per launch
- * where the kernels allow (lbem_steps_per_launch); walls, an absorber,
- * dispersion or anisotropy make every launch a single step.  The result does
- * not depend on this choice (bit for bit). */
+ * amp[k] at time t0 + k.  ESTATE before lbem_init_fields.  Handles with pull
+ * streaming advance several steps per launch where the kernels allow
+ * (lbem_steps_per_launch); walls, anisotropy and, but for 3D FP32, an absorber
+ * or dispersion make every launch a single step.  The result does not depend on
+ * this choice (bit for bit).  The state moves to its other copy with every
+ * launch; under stream capture launches are chosen so that a graph of an even
+ * number of steps of a handle that has taken a step ends in the copy that it
+ * began with, and can be replayed. */
 int lbem_step(lbem_t h, int64_t nsteps, const double* amp);
 
 /* E and B at the current time (3*n doubles each, component-major), recovered
@@ -193,9 +196,8 @@ int64_t lbem_time(lbem_t h);
 
 /* Time steps advanced per kernel launch by lbem_step on this handle (1, or 2-4
  * when several steps are fused into one pass: 2D in every format but plain
- * FP16 and 3D FP32 by default, the 3D 16-bit formats two steps when the
- * environment variable LBEM_DEV3F=1 is set at creation; the result is
- * identical to single steps).
+ * FP16, 3D FP32 and the 3D 16-bit formats where the lattice is large enough for
+ * the tiles of two steps; the result is identical to single steps).
  * EINVAL for NULL. */
 int lbem_steps_per_launch(lbem_t h);
 
@@ -295,7 +297,9 @@ const char* lbem_strerror(int code);
  * is one persistent launch per (dim, format) class that strides over all
  * (lattice, tile) work items of the handles in that class.  A tick is
  * steps_per_tick such steps; each class's steps are captured once, when the
- * batch is created, as a HIP graph, and the classes present are replayed; the per-lattice table it reads is uploaded before each
+ * batch is created, as a HIP graph, and the classes present are replayed
+ * (classes that take several steps per launch are launched directly); the
+ * per-lattice table it reads is uploaded before each
  * tick, so lattices can join and leave between ticks.  Results are bit-for-bit
  * those of lbem_step on each handle alone.
  */

@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "march2d.h"
 #include "pair3d.h"
+#include "pair3f.h"
 
 using namespace lbem;
 
@@ -157,6 +158,7 @@ struct lbem_s {
     unsigned msrc_mask[8];
     int64_t nmsrc;       // source segments of the strips
     int f3_tx, f3_ty, f3_lz;
+    bool pair_f32, pair_ext; // 3D FP32 pairs on pgeo: without extras, with an absorber or a pole
     Geo fgeo;
     // 3D 16-bit formats: two steps per launch (k_pair_dev3) and its source
     // segments
@@ -210,6 +212,7 @@ struct lbem_s {
     // frequency-dispersive permittivity (one Lorentz pole per cell)
     void* ade;               // [3][n] coefficients, handle-owned, or nullptr
     void* pol;               // [2P][n] auxiliary P and J per pair
+    void* pol2;              // the buffer a two-step launch writes them to (they swap), or nullptr
     // anisotropy (plain formats): [D][n] ratios r_a, handle-owned; valid while ra_set
     void* ra;
     bool ra_set;
@@ -433,9 +436,61 @@ static hipError_t go_fused3(lbem_s* h, const T* src, T* dst, const double* amp)
 // formats with a multi-step kernel: all but plain FP16
 static bool fused_format(const lbem_s* h) { return h->prec <= LBEM_F32 || is_dev(h->prec); }
 
-static bool fused_ok(const lbem_s* h)
+// steps per launch of lbem_step
+static int fused_steps(const lbem_s* h)
 {
-    return fused_format(h) && h->streaming == LBEM_STREAM_PULL && h->fuse_ns > 1 && !has_bx(h);
+    if (!fused_format(h) || h->streaming != LBEM_STREAM_PULL) return 1;
+    if (!has_bx(h)) return h->fuse_ns;
+    // 3D FP32 with an absorber or a pole, no walls and no anisotropy
+    return h->pair_ext && !h->ra_set && !ext_of(h).walls() && (!h->ade || h->pol2) ? 2 : 1;
+}
+
+// 3D FP32 pairs on the 62 x 14 tiles
+template <bool MU, bool EXT, bool TH>
+static hipError_t launch_pair_f32(lbem_s* h, const float* src, float* dst, const AmpPack<float, 2>& a, const PairExt& ex)
+{
+    PairSrc ps;
+    ps.flag = h->psrc_flag;
+    ps.idx = h->psrc_idx;
+    ps.val = h->psrc_val;
+    ps.pair = h->psrc_pair;
+    if (h->nts)
+        hipLaunchKernelGGL((k_pair_f32<MU, EXT, TH, true>), dim3(h->pgeo.nblocks), dim3(1024), 0, h->stream, src, dst,
+                           (const float*)h->cl2, (const float*)h->dlnmu, h->pgeo, ps, a, (float)(1.0 / h->cfg.tau),
+                           (int)TH, ex);
+    else
+        hipLaunchKernelGGL((k_pair_f32<MU, EXT, TH, false>), dim3(h->pgeo.nblocks), dim3(1024), 0, h->stream, src, dst,
+                           (const float*)h->cl2, (const float*)h->dlnmu, h->pgeo, ps, a, (float)(1.0 / h->cfg.tau),
+                           (int)TH, ex);
+    return hipGetLastError();
+}
+
+static hipError_t go_pair_f32(lbem_s* h, const float* src, float* dst, const double* amp)
+{
+    AmpPack<float, 2> a;
+    for (int j = 0; j < 2; ++j) a.a[j] = (float)(amp ? amp[j] : 0.0);
+    PairExt ex;
+    ex.keep = (const float*)h->keep;
+    ex.ade = (const float*)h->ade;
+    ex.pin = (const float*)h->pol;
+    ex.pout = (float*)h->pol2;
+    const bool th = h->cfg.tau == 0.5;
+    if (!has_bx(h)) {
+        if (h->mu_set)
+            return th ? launch_pair_f32<true, false, true>(h, src, dst, a, ex)
+                      : launch_pair_f32<true, false, false>(h, src, dst, a, ex);
+        return th ? launch_pair_f32<false, false, true>(h, src, dst, a, ex)
+                  : launch_pair_f32<false, false, false>(h, src, dst, a, ex);
+    }
+    hipError_t e;
+    if (h->mu_set)
+        e = th ? launch_pair_f32<true, true, true>(h, src, dst, a, ex)
+               : launch_pair_f32<true, true, false>(h, src, dst, a, ex);
+    else
+        e = th ? launch_pair_f32<false, true, true>(h, src, dst, a, ex)
+               : launch_pair_f32<false, true, false>(h, src, dst, a, ex);
+    if (h->ade) std::swap(h->pol, h->pol2);
+    return e;
 }
 
 // plain formats: populations stored as S, arithmetic in T
@@ -522,6 +577,8 @@ struct PlainImpl : Impl {
             T* b = (T*)h->pop[1 - h->cur];
             hipError_t e;
             if constexpr (D == 2) e = go_fused<T>(h, a, b, amp, ns);
+            else if constexpr (std::is_same<T, float>::value)
+                e = h->pair_f32 || has_bx(h) ? go_pair_f32(h, a, b, amp) : go_fused3<T>(h, a, b, amp);
             else e = go_fused3<T>(h, a, b, amp);
             h->cur = 1 - h->cur;
             return e;

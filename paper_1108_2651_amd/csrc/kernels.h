@@ -115,6 +115,14 @@ struct CellExt {
     __host__ __device__ bool walls() const { return (kind[0] | kind[1] | kind[2]) != 0; }
 };
 
+// P and J of one pair of a cell advance by one step
+template <typename T>
+__device__ __forceinline__ void ade_advance(T c1, T c2, T c3, T cl2, T rho, T& P, T& J)
+{
+    J = c1 * J - c2 * (cl2 * rho) - c3 * P;
+    P = P + J;
+}
+
 // the dispersion update of one cell: new J per pair (the caller adds J/c^2 to
 // the rest particle after collision)
 template <int D, typename T>
@@ -127,10 +135,10 @@ __device__ __forceinline__ void ade_update(const CellExt& bc, int64_t n, int c, 
     const T c1 = co[c], c2 = co[n + c], c3 = co[2 * n + c];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const T Po = st[(int64_t)p * n + c], Jo = st[(int64_t)(P + p) * n + c];
-        const T J = c1 * Jo - c2 * (cl2 * rho[p]) - c3 * Po;
+        T Pp = st[(int64_t)p * n + c], J = st[(int64_t)(P + p) * n + c];
+        ade_advance<T>(c1, c2, c3, cl2, rho[p], Pp, J);
         Jn[p] = J;
-        st[(int64_t)p * n + c] = Po + J;
+        st[(int64_t)p * n + c] = Pp;
         st[(int64_t)(P + p) * n + c] = J;
     }
 }
@@ -1774,6 +1782,7 @@ struct MarchGeo {
 struct PairGeo {
     int nx, ny, nz;
     int tiles_x, tiles_y, lz;            // planes per chunk
+    int sx, sy;                          // columns and rows a tile stores (FP32)
     int nblocks, xcd;
     int64_t n;
 };

@@ -142,6 +142,49 @@ static void make_pair_geo(lbem_s* h)
     f.nblocks = env_int("LBEM_FIELDS3", share >= 0.27) ? f.tiles_x * f.tiles_y * ((f.nz + f.lz - 1) / f.lz) : 0;
 }
 
+// Two steps per launch for 3D FP32 on the tiles of k_pair_f32, up to 64 x 13
+// stored cells, one block per CU.  Columns go by 64 (rows then start on whole
+// lines wherever the lattice's do: 160^3 21.6 ps per update, three even tiles
+// of 54 columns 30.1), rows evenly.
+static void make_pairf_geo(lbem_s* h)
+{
+    PairGeo& g = h->pgeo;
+    g.nx = (int)h->cfg.nx; g.ny = (int)h->cfg.ny; g.nz = (int)h->cfg.nz; g.n = h->n;
+    g.sx = std::min(g.nx, PFX);
+    g.tiles_x = (g.nx + g.sx - 1) / g.sx;
+    g.tiles_y = (g.ny + PFY - 1) / PFY;
+    g.sy = (g.ny + g.tiles_y - 1) / g.tiles_y;
+    const int64_t cus = device_cus(), cols = (int64_t)g.tiles_x * g.tiles_y;
+    g.lz = std::max(1, env_int("LBEM_FUSE3_LZ", march_planes(cols, g.nz, cus, 2)));
+    g.nblocks = (int)(cols * ((g.nz + g.lz - 1) / g.lz));
+    g.xcd = env_int("LBEM_FUSE3_XCD", std::max(2, g.tiles_x));
+    const bool fits = (int64_t)g.nx * g.ny < ((int64_t)1 << 30);       // 32-bit offsets within a plane
+    // With extras, and below FUSE3D_MIN cells without: where at least a quarter
+    // of the work is on stored cells.  Measured, us per step, single / pair
+    // (share), with a pole: 48^3 (0.09) 7.1 / 10.8, 64^3 (0.21) 10.6 / 13.6,
+    // 20x200x200 (0.25) 34.6 / 27.4, 72^3 (0.29) 15.8 / 13.4, 100^3 (0.52) 36.3
+    // / 28.2, 160^3 153 / 124, 256^3 683 / 432, 250x190x171 431 / 246, 384^3
+    // 2565 / 1567; with an absorber 256^3 478 / 318; with neither 64^3 8.5 /
+    // 10.2, 72^3 11.6 / 10.0, 61x100x100 (0.48) 16.9 / 12.5.
+    const double share = (double)g.n / ((double)((g.nblocks + cus - 1) / cus) * cus * (g.lz + 2) * (PFX * PFY));
+    h->pair_ext = fits && env_int("LBEM_FUSE3", share >= 0.25 ? 2 : 1) == 2;
+    if ((double)h->n < FUSE3D_MIN) h->fuse_ns = h->pair_ext ? 2 : 1;
+    // Without extras the column tiles of k_step_fused3d stay, from FUSE3D_MIN
+    // cells on, for up to 4e6 cells whose rows are several tiles and no whole
+    // 64-byte sectors (us per step, those / these: 90x150x150 57 / 63,
+    // 124x126x128 45 / 49, 150^3 91 / 98, though 140x120x110 58 / 54), and for up
+    // to 3e7 cells where every axis is whole 128s, so that those tiles and
+    // chunks are all full (128^3 46.1 / 47.2, 256^3 303.6 / 303.4, with a
+    // source 306 / 311).  Elsewhere these are faster: 112^3 27.4 / 23.7, 144^3
+    // 77 / 68, 160^3 97 / 88, 256x100x100 61 / 51, 256x256x60 83 / 76,
+    // 48x200x200 50 / 38, 250x190x171 212 / 172 (with a source 181), 320^3 622
+    // / 590, 512^3 2529 / 2422.
+    const bool odd = (double)h->n >= FUSE3D_MIN && ((g.tiles_x > 1 && g.nx % 16 != 0 && (double)h->n < 4.0e6) ||
+                                                    ((g.nx | g.ny | g.nz) % 128 == 0 && (double)h->n < 3.0e7));
+    const bool asked = std::getenv("LBEM_FUSE3_TX") != nullptr || std::getenv("LBEM_FUSE3_TY") != nullptr;
+    h->pair_f32 = fits && env_int("LBEM_PAIR3F", !odd && !asked) != 0;
+}
+
 static void make_fused_geo(lbem_s* h)
 {
     if (h->D == 3 && is_dev(h->prec)) {
@@ -150,6 +193,7 @@ static void make_fused_geo(lbem_s* h)
     }
     if (h->D == 3) {
         make_fused3_geo(h);
+        if (h->prec == LBEM_F32) make_pairf_geo(h);
         return;
     }
     // Four steps per launch in every format but plain FP16, at every size, with
@@ -716,18 +760,20 @@ static int build_xrow_source(lbem_s* h, const std::vector<std::pair<int64_t, dou
 static int build_pair_source(lbem_s* h, const std::vector<std::pair<int64_t, double>>& cells, int pp)
 {
     const PairGeo& g = h->pgeo;
+    const bool f32 = h->prec == LBEM_F32;
+    const int tw = f32 ? g.sx : PRX, th = f32 ? g.sy : PRY, halo = f32 ? 1 : 2, len = f32 ? PFSEG : 64;
     const size_t plane = (size_t)g.ny * g.nz;
     std::vector<int> idx((size_t)g.tiles_x * plane, -1);
     std::vector<unsigned char> flag((size_t)g.nblocks, 0);
     // per row and plane the tiles and chunks whose frame (the stored rows and
-    // planes and two more on each side, periodic images included) holds it
-    auto frames = [](int n, int step, int count) {
+    // planes and the halo on each side, periodic images included) holds it
+    auto frames = [halo](int n, int step, int count) {
         std::vector<std::vector<int>> of(n);
         for (int t = 0; t < count; ++t)
-            for (int j = 0; j < std::min(n, step + 4); ++j) of[(((t * step - 2 + j) % n) + n) % n].push_back(t);
+            for (int j = 0; j < std::min(n, step + 2 * halo); ++j) of[(((t * step - halo + j) % n) + n) % n].push_back(t);
         return of;
     };
-    const auto tiles = frames(g.ny, PRY, g.tiles_y), chunks = frames(g.nz, g.lz, (g.nz + g.lz - 1) / g.lz);
+    const auto tiles = frames(g.ny, th, g.tiles_y), chunks = frames(g.nz, g.lz, (g.nz + g.lz - 1) / g.lz);
     std::vector<float> val, row(g.nx, 0.f);
     int segs = 0;
     for (size_t k = 0; k < cells.size();) {        // cells are sorted: one row at a time
@@ -736,18 +782,18 @@ static int build_pair_source(lbem_s* h, const std::vector<std::pair<int64_t, dou
         size_t e = k;
         for (; e < cells.size() && cells[e].first / g.nx == r; ++e) row[cells[e].first % g.nx] = (float)cells[e].second;
         for (int t = 0; t < g.tiles_x; ++t) {
-            int gx = (t * PRX - 2) % g.nx;
+            int gx = (t * tw - halo) % g.nx;
             if (gx < 0) gx += g.nx;
-            float seg[64];
+            float seg[PFSEG];
             bool any = false;
-            for (int j = 0; j < 64; ++j) {
+            for (int j = 0; j < len; ++j) {
                 seg[j] = row[gx];
                 any = any || seg[j] != 0.f;
                 gx = gx + 1 == g.nx ? 0 : gx + 1;
             }
             if (!any) continue;
             idx[(size_t)t * plane + (size_t)z * g.ny + y] = segs++;
-            val.insert(val.end(), seg, seg + 64);
+            val.insert(val.end(), seg, seg + len);
             for (int ty : tiles[y])
                 for (int zc : chunks[z]) flag[((size_t)zc * g.tiles_y + ty) * g.tiles_x + t] = 1;
         }
@@ -829,6 +875,7 @@ int lbem_destroy(lbem_t h)
     if (h->keep) (void)hipFree(h->keep);
     if (h->ade) (void)hipFree(h->ade);
     if (h->pol) (void)hipFree(h->pol);
+    if (h->pol2) (void)hipFree(h->pol2);
     if (h->ra) (void)hipFree(h->ra);
     // stream-ordered: returns the memory without waiting for the whole device
     if (h->partials) (void)hipFreeAsync(h->partials, h->stream);
@@ -972,7 +1019,8 @@ int lbem_set_dispersion(lbem_t h, const double* wp2, const double* w02, const do
     if (!wp2) {
         if (h->ade) (void)hipFree(h->ade);
         if (h->pol) (void)hipFree(h->pol);
-        h->ade = h->pol = nullptr;
+        if (h->pol2) (void)hipFree(h->pol2);
+        h->ade = h->pol = h->pol2 = nullptr;
         return LBEM_OK;
     }
     if (h->streaming != LBEM_STREAM_PULL) return LBEM_EINVAL;
@@ -1001,6 +1049,11 @@ int lbem_set_dispersion(lbem_t h, const double* wp2, const double* w02, const do
             (void)hipFree(h->ade);
             h->ade = h->pol = nullptr;
             return LBEM_ENOMEM;
+        }
+        // two-step launches need a second copy; without it the steps stay single
+        if (h->pair_ext && hipMalloc(&h->pol2, pb) != hipSuccess) {
+            h->pol2 = nullptr;
+            (void)hipGetLastError();
         }
     }
     if (hipMemcpyAsync(h->ade, host.data(), (size_t)3 * n * tm, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
@@ -1148,7 +1201,14 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
         const int rc = build_xrow_source(h, cv, pp);
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
-    if (fused_format(h) && h->fuse_ns > 1) {
+    const bool pair32 = D == 3 && h->prec == LBEM_F32;
+    if (pair32 && (h->pair_ext || h->pair_f32)) {
+        std::vector<std::pair<int64_t, double>> cv(merged.size());
+        for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
+        const int rc = build_pair_source(h, cv, pp);
+        if (rc != LBEM_OK) { free_source(h); return rc; }
+    }
+    if (fused_format(h) && h->fuse_ns > 1 && !(pair32 && h->pair_f32)) {
         int rc;
         if (D == 2 || is_dev(h->prec)) {
             std::vector<std::pair<int64_t, double>> cv(merged.size());
@@ -1169,12 +1229,26 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     if (!h || nsteps < 0) return LBEM_EINVAL;
     if (!h->have_fields) return LBEM_ESTATE;
     HIP_OK(follow_ticks(h));
-    const bool fuse = fused_ok(h);
-    int64_t k = 0;
+    const int nf = fused_steps(h);
+    // Under stream capture the state ends in the buffer that single steps would
+    // leave it in, so that a graph of an even number of steps can be replayed:
+    // full launches by twos, the rest singly.
+    bool captured = false;
+    if (nf > 1 && nsteps > 1) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
+        captured = st != hipStreamCaptureStatusNone;
+    }
+    int64_t k = 0, twos = 0;
     while (k < nsteps) {
-        // 2D launches take any number of steps from two to fuse_ns
-        const int64_t ns = std::min<int64_t>(h->fuse_ns, nsteps - k);
-        if (fuse && h->layout == LAYOUT_PULL_PENDING && (h->D == 2 ? ns >= 2 : ns == h->fuse_ns)) {
+        // 2D launches take any number of steps from two to nf
+        int64_t ns = std::min<int64_t>(nf, nsteps - k);
+        if (captured) {
+            if (twos == 0 && h->layout == LAYOUT_PULL_PENDING && nsteps - k >= 2 * nf) twos = 2;
+            if (twos > 0) --twos;
+            else ns = 1;
+        }
+        if (ns > 1 && h->layout == LAYOUT_PULL_PENDING && (h->D == 2 || ns == nf)) {
             if (h->impl->step_fused(h, (amp && h->nsrc) ? amp + k : nullptr, (int)ns) != hipSuccess)
                 return LBEM_EDEVICE;
             k += ns;
@@ -1267,7 +1341,7 @@ int64_t lbem_time(lbem_t h) { return h ? h->t : -1; }
 int lbem_steps_per_launch(lbem_t h)
 {
     if (!h) return LBEM_EINVAL;
-    return fused_ok(h) ? h->fuse_ns : 1;
+    return fused_steps(h);
 }
 
 namespace {
