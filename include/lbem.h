@@ -149,8 +149,9 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
  * source) gives the source amplitude of each step: step k of this call uses
  * amp[k] at time t0 + k.  ESTATE before lbem_init_fields.  Handles with pull
  * streaming advance several steps per launch where the kernels allow
- * (lbem_steps_per_launch); walls, anisotropy and, but for 3D FP32, an absorber
- * or dispersion make every launch a single step.  The result does not depend on
+ * (lbem_steps_per_launch): also with an absorber or dispersion in FP32 and in 2D
+ * FP64, and with walls in 2D FP32 and FP64; elsewhere these, and anisotropy
+ * everywhere, make every launch a single step.  The result does not depend on
  * this choice (bit for bit).  The state moves to its other copy with every
  * launch; under stream capture launches are chosen so that a graph of an even
  * number of steps of a handle that has taken a step ends in the copy that it

@@ -153,12 +153,15 @@ struct lbem_s {
     int fuse_ns;
     MarchGeo mgeo;
     int mcpl, mwpb;
+    MarchGeo mgeo_x[2];      // the same with walls or an absorber, and with a pole (more registers)
+    int mwpb_x[2];
     int* msrc_idx;
     void* msrc_val;
     unsigned msrc_mask[8];
     int64_t nmsrc;       // source segments of the strips
     int f3_tx, f3_ty, f3_lz;
-    bool pair_f32, pair_ext; // 3D FP32 pairs on pgeo: without extras, with an absorber or a pole
+    bool pair_f32;           // 3D FP32 without extras: pairs on pgeo
+    int ext_ns;              // steps per launch with extras (plain formats; 1 = off)
     Geo fgeo;
     // 3D 16-bit formats: two steps per launch (k_pair_dev3) and its source
     // segments
@@ -337,9 +340,25 @@ static hipError_t launch_fields(lbem_s* h, const R& rd, double* E, double* B, do
     return hipGetLastError();
 }
 
+template <typename T>
+static MarchExt<T> march_ext(const lbem_s* h)
+{
+    MarchExt<T> e{};
+    const CellExt b = ext_of(h);
+    e.wx = b.kind[0] != 0;
+    e.wy = b.kind[1] != 0;
+    e.nx_ = e.wx && (b.kind[0] == 1) == (pair_a(2, 0) == 0 || pair_b(2, 0) == 0);
+    e.ny_ = e.wy && (b.kind[1] == 1) == (pair_a(2, 0) == 1 || pair_b(2, 0) == 1);
+    e.keep = (const T*)h->keep;
+    e.ade = (const T*)h->ade;
+    e.pin = (const T*)h->pol;
+    e.pout = (T*)h->pol2;
+    return e;
+}
+
 // 2D multi-step launches (k_march2d).  The paper's tau = 1/2 gets its own
 // instantiation: the reflection collision folds at compile time.
-template <class IO, int NS, int CPL, bool MU, bool TH>
+template <class IO, int NS, int CPL, bool MU, bool TH, int EXT = 0>
 static void launch_march(lbem_s* h, const IO& io, const double* amp)
 {
     typedef typename IO::T T;
@@ -349,9 +368,11 @@ static void launch_march(lbem_s* h, const IO& io, const double* amp)
     for (int k = 0; k < 8; ++k) ms.mask[k] = h->nmsrc ? h->msrc_mask[k] : 0u;
     AmpPack<T, NS> a;
     for (int j = 0; j < NS; ++j) a.a[j] = (T)(amp ? amp[j] : 0.0);
-    hipLaunchKernelGGL((k_march2d<IO, NS, CPL, MU, TH>), dim3(h->mgeo.nblocks), dim3(64 * h->mwpb), 0, h->stream, io,
-                       (const T*)h->cl2, (const T*)h->dlnmu, h->mgeo, ms, a, (T)(1.0 / h->cfg.tau),
-                       (int)(h->cfg.tau == 0.5));
+    const MarchGeo& g = EXT ? h->mgeo_x[EXT ? EXT - 1 : 0] : h->mgeo;
+    const int wpb = EXT ? h->mwpb_x[EXT ? EXT - 1 : 0] : h->mwpb;
+    hipLaunchKernelGGL((k_march2d<IO, NS, CPL, MU, TH, EXT>), dim3(g.nblocks), dim3(64 * wpb), 0, h->stream, io,
+                       (const T*)h->cl2, (const T*)h->dlnmu, g, ms, a, (T)(1.0 / h->cfg.tau),
+                       (int)(h->cfg.tau == 0.5), march_ext<T>(h));
 }
 
 template <class IO, int NS, int CPL, bool MU>
@@ -380,13 +401,35 @@ static hipError_t go_march(lbem_s* h, const IO& io, const double* amp, int ns)
     return hipGetLastError();
 }
 
+// with walls, an absorber or a pole: launches of four and two
+template <class IO, int CPL, bool MU>
+static hipError_t go_march_ext(lbem_s* h, const IO& io, const double* amp, int ns)
+{
+    if (ns == 4 && h->ade) launch_march<IO, 4, CPL, MU, false, 2>(h, io, amp);
+    else if (ns == 4) launch_march<IO, 4, CPL, MU, false, 1>(h, io, amp);
+    else if (ns == 2 && h->ade) launch_march<IO, 2, CPL, MU, false, 2>(h, io, amp);
+    else if (ns == 2) launch_march<IO, 2, CPL, MU, false, 1>(h, io, amp);
+    else return hipErrorInvalidValue;
+    if (h->ade) std::swap(h->pol, h->pol2);
+    return hipGetLastError();
+}
+
+template <typename T, int CPL>
+static hipError_t go_fused_c(lbem_s* h, const T* src, T* dst, const double* amp, int ns)
+{
+    typedef MarchPlain<T, CPL> IO;
+    const IO io{src, dst, h->n};
+    if (!has_bx(h)) return go_march<IO, CPL>(h, io, amp, ns);
+    return h->mu_set ? go_march_ext<IO, CPL, true>(h, io, amp, ns) : go_march_ext<IO, CPL, false>(h, io, amp, ns);
+}
+
 template <typename T>
 static hipError_t go_fused(lbem_s* h, const T* src, T* dst, const double* amp, int ns)
 {
     if constexpr (sizeof(T) == 4) {
-        if (h->mcpl == 2) return go_march<MarchPlain<T, 2>, 2>(h, MarchPlain<T, 2>{src, dst, h->n}, amp, ns);
+        if (h->mcpl == 2) return go_fused_c<T, 2>(h, src, dst, amp, ns);
     }
-    return go_march<MarchPlain<T, 1>, 1>(h, MarchPlain<T, 1>{src, dst, h->n}, amp, ns);
+    return go_fused_c<T, 1>(h, src, dst, amp, ns);
 }
 
 template <typename T, int TX, int TY, bool MU, bool NTS>
@@ -441,8 +484,8 @@ static int fused_steps(const lbem_s* h)
 {
     if (!fused_format(h) || h->streaming != LBEM_STREAM_PULL) return 1;
     if (!has_bx(h)) return h->fuse_ns;
-    // 3D FP32 with an absorber or a pole, no walls and no anisotropy
-    return h->pair_ext && !h->ra_set && !ext_of(h).walls() && (!h->ade || h->pol2) ? 2 : 1;
+    // walls (2D), an absorber or a pole, no anisotropy
+    return !h->ra_set && (h->D == 2 || !ext_of(h).walls()) && (!h->ade || h->pol2) ? std::max(1, h->ext_ns) : 1;
 }
 
 // 3D FP32 pairs on the 62 x 14 tiles

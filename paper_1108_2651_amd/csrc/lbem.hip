@@ -167,8 +167,8 @@ static void make_pairf_geo(lbem_s* h)
     // 2565 / 1567; with an absorber 256^3 478 / 318; with neither 64^3 8.5 /
     // 10.2, 72^3 11.6 / 10.0, 61x100x100 (0.48) 16.9 / 12.5.
     const double share = (double)g.n / ((double)((g.nblocks + cus - 1) / cus) * cus * (g.lz + 2) * (PFX * PFY));
-    h->pair_ext = fits && env_int("LBEM_FUSE3", share >= 0.25 ? 2 : 1) == 2;
-    if ((double)h->n < FUSE3D_MIN) h->fuse_ns = h->pair_ext ? 2 : 1;
+    h->ext_ns = fits && env_int("LBEM_FUSE3", share >= 0.25 ? 2 : 1) == 2 ? 2 : 1;
+    if ((double)h->n < FUSE3D_MIN) h->fuse_ns = h->ext_ns;
     // Without extras the column tiles of k_step_fused3d stay, from FUSE3D_MIN
     // cells on, for up to 4e6 cells whose rows are several tiles and no whole
     // 64-byte sectors (us per step, those / these: 90x150x150 57 / 63,
@@ -183,6 +183,32 @@ static void make_pairf_geo(lbem_s* h)
                                                     ((g.nx | g.ny | g.nz) % 128 == 0 && (double)h->n < 3.0e7));
     const bool asked = std::getenv("LBEM_FUSE3_TX") != nullptr || std::getenv("LBEM_FUSE3_TY") != nullptr;
     h->pair_f32 = fits && env_int("LBEM_PAIR3F", !odd && !asked) != 0;
+}
+
+// Strips and chunks of the 2D march for `waves` resident waves per SIMD.
+static void make_march_chunks(const lbem_s* h, int waves, MarchGeo& g, int& wpb)
+{
+    const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
+    g.nx = nx; g.ny = ny; g.n = h->n;
+    const int ow = 64 * h->mcpl - 2 * MARCH_HX;
+    g.strips = (nx + ow - 1) / ow;
+    // Rows per chunk: whole rounds of the waves that are resident, about 24
+    // rows each: a chunk reads 8 rows beyond its own, a thin last round leaves
+    // CUs idle.  FP32 2048^2, rows -> us per launch: 8 34.2, 16 33.4, 19 31.8 (3996 waves), 24
+    // 35.2, 40 31.8 (1924), 64 36.0.  Small lattices: as many waves as give
+    // two rows each, where a launch is a few rows of latency (256^2: 2 rows
+    // 4.2, 4 4.8, 8 5.9).
+    const int64_t slots = 1024 * waves;
+    const int64_t want = std::max<int64_t>(1, ((int64_t)g.strips * ny + slots - 1) / slots);  // rows if all fit
+    const int64_t rounds = (want + 23) / 24;
+    const int64_t per = rounds * slots;
+    const int64_t chunks = std::max<int64_t>(1, per / g.strips);     // that fit these rounds
+    g.rows = (int)std::min<int64_t>(ny, std::max<int64_t>(2, (ny + chunks - 1) / chunks));
+    g.nwork = g.strips * ((ny + g.rows - 1) / g.rows);
+    // few waves: one per block, so that they spread over the CUs (96x64 3.6
+    // against 4.0 us per launch)
+    wpb = g.nwork <= 1024 ? 1 : 4;
+    g.nblocks = ((g.nwork + wpb - 1) / wpb + 7) / 8 * 8;
 }
 
 static void make_fused_geo(lbem_s* h)
@@ -203,6 +229,7 @@ static void make_fused_geo(lbem_s* h)
     const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
     h->fuse_ns = env_int("LBEM_FUSE", 4);
     if (h->fuse_ns < 1 || h->fuse_ns > 4) h->fuse_ns = 1;
+    h->ext_ns = h->prec <= LBEM_F32 && h->n >= 4096 ? (h->fuse_ns >= 4 ? 4 : (h->fuse_ns >= 2 ? 2 : 1)) : 1;
     // FP32 lattices of 8e6 cells and more, rows of even length: two cells per
     // lane.  One eighth of the columns is recomputed with one cell per lane,
     // one sixteenth with two, which shows once the state streams from HBM (us
@@ -211,27 +238,18 @@ static void make_fused_geo(lbem_s* h)
     // (2048^2 31.8 / 32.2, 1000^2 10.8 / 12.9).  FP64 keeps one: two need more
     // than 256 registers.
     h->mcpl = h->prec == LBEM_F32 && nx % 2 == 0 && (double)h->n >= 8.0e6 ? 2 : 1;
-    MarchGeo& g = h->mgeo;
-    g.nx = nx; g.ny = ny; g.n = h->n;
-    const int ow = 64 * h->mcpl - 2 * MARCH_HX;
-    g.strips = (nx + ow - 1) / ow;
-    // Rows per chunk: whole rounds of the waves that are resident (four per
-    // SIMD with one cell per lane, two with two), about 24 rows each: a chunk
-    // reads 8 rows beyond its own, a thin last round leaves CUs idle.  FP32
-    // 2048^2, rows -> us per launch: 8 34.2, 16 33.4, 19 31.8 (3996 waves), 24
-    // 35.2, 40 31.8 (1924), 64 36.0.  Small lattices: as many waves as give
-    // two rows each, where a launch is a few rows of latency (256^2: 2 rows
-    // 4.2, 4 4.8, 8 5.9).
-    const int64_t slots = 1024 * (h->mcpl == 2 ? 2 : 4);
-    const int64_t want = std::max<int64_t>(1, ((int64_t)g.strips * ny + slots - 1) / slots);  // rows if all fit
-    const int64_t rounds = (want + 23) / 24;
-    const int64_t per = rounds * slots;
-    g.rows = (int)std::min<int64_t>(ny, std::max<int64_t>(2, ((int64_t)g.strips * ny + per - 1) / per));
-    g.nwork = g.strips * ((ny + g.rows - 1) / g.rows);
-    // few waves: one per block, so that they spread over the CUs (96x64 3.6
-    // against 4.0 us per launch)
-    h->mwpb = g.nwork <= 1024 ? 1 : 4;
-    g.nblocks = ((g.nwork + h->mwpb - 1) / h->mwpb + 7) / 8 * 8;
+    // With walls, an absorber or a pole FP32 and FP64 take launches of four and
+    // two.  us per step, single steps / these: FP32 walls 128^2 2.7 / 1.7,
+    // 1023x767 7.7 / 4.0, 2048^2 27.7 / 10.3, 4096^2 113 / 45; with an absorber
+    // 4096^2 121 / 49; a pole 128^2 2.9 / 2.0, 2048^2 43 / 19, 4096^2 228 / 88;
+    // FP64 walls 2048^2 60 / 23, a pole 87 / 41.  Boxes below 4096 cells, where
+    // a call is its launches, keep lbem_steps_per_launch of one.
+    // Waves resident per SIMD without extras, with walls or an absorber and with
+    // a pole, by their registers (one / two cells per lane in FP32, FP64).
+    const int w1 = h->prec == LBEM_F64 ? 2 : 4, w2 = h->prec == LBEM_F64 ? 1 : 3;
+    make_march_chunks(h, h->mcpl == 2 ? 2 : 4, h->mgeo, h->mwpb);
+    make_march_chunks(h, h->mcpl == 2 ? 2 : w1, h->mgeo_x[0], h->mwpb_x[0]);
+    make_march_chunks(h, h->mcpl == 2 ? 1 : w2, h->mgeo_x[1], h->mwpb_x[1]);
 }
 
 static void make_zmarch_geo(lbem_s* h)
@@ -1051,7 +1069,7 @@ int lbem_set_dispersion(lbem_t h, const double* wp2, const double* w02, const do
             return LBEM_ENOMEM;
         }
         // two-step launches need a second copy; without it the steps stay single
-        if (h->pair_ext && hipMalloc(&h->pol2, pb) != hipSuccess) {
+        if (h->ext_ns > 1 && hipMalloc(&h->pol2, pb) != hipSuccess) {
             h->pol2 = nullptr;
             (void)hipGetLastError();
         }
@@ -1202,7 +1220,7 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
     const bool pair32 = D == 3 && h->prec == LBEM_F32;
-    if (pair32 && (h->pair_ext || h->pair_f32)) {
+    if (pair32 && (h->ext_ns > 1 || h->pair_f32)) {
         std::vector<std::pair<int64_t, double>> cv(merged.size());
         for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
         const int rc = build_pair_source(h, cv, pp);
@@ -1230,6 +1248,7 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     if (!h->have_fields) return LBEM_ESTATE;
     HIP_OK(follow_ticks(h));
     const int nf = fused_steps(h);
+    const bool ext2 = h->D == 2 && has_bx(h);    // launches of four and two steps only
     // Under stream capture the state ends in the buffer that single steps would
     // leave it in, so that a graph of an even number of steps can be replayed:
     // full launches by twos, the rest singly.
@@ -1241,8 +1260,9 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     }
     int64_t k = 0, twos = 0;
     while (k < nsteps) {
-        // 2D launches take any number of steps from two to nf
+        // 2D launches take any number of steps from two to nf (no three with extras)
         int64_t ns = std::min<int64_t>(nf, nsteps - k);
+        if (ext2 && ns == 3) ns = 2;
         if (captured) {
             if (twos == 0 && h->layout == LAYOUT_PULL_PENDING && nsteps - k >= 2 * nf) twos = 2;
             if (twos > 0) --twos;

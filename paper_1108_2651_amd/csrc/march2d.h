@@ -19,6 +19,11 @@
 // the first and the last step encodes its result as it would be stored and
 // decodes that in registers, as every reader would.
 //
+// Walls, an absorbing layer and a dispersion pole (plain formats) are applied at
+// every level: what a wall reflects is in the cell's own registers, sigma, the
+// pole's coefficients, P and J ride in the ring of rows, and P and J go to a
+// second buffer with the last level.
+//
 // What bounds it: 21.5 VALU instructions per update (one cell, one step)
 // against 74 of the LDS-frame kernel it replaces, so the state's bytes do.
 // Measured per launch of four steps, LDS frame (64x16 tiles, 512 threads) ->
@@ -29,6 +34,8 @@
 // FP16-dev 113 -> 32 us (12 B per update at 2.8 TB/s: VALU bound, about 90
 // instructions per update for encoding and decoding), FP16 ghost 20 us.  They
 // take one cell per lane (two need more than 256 registers: 32 against 37 us).
+// With extras, single steps -> this kernel: 40 steps of FP32 1023x767 with walls
+// and an absorber 368 -> 196 us (116 VGPRs, 4 waves per SIMD; a pole 153).
 #pragma once
 #include "kernels.h"
 
@@ -183,14 +190,28 @@ struct MarchDev {
     }
 };
 
-// One work item: strip x chunk.  SRC: the chunk holds source cells.
-template <class IO, int NS, int CPL, bool MU, bool TH, bool SRC, bool UP>
+// Cell-local extras (plain formats).  Walls: a population that would enter from
+// beyond one is the cell's own outgoing one of the level before, negated or not;
+// rows and columns past a wall run on wrapped data that nothing stored depends on.
+template <typename T>
+struct MarchExt {
+    bool wx, wy, nx_, ny_;   // walls on the axis, and whether they negate
+    const T* keep;       // per-cell 1 - sigma, or nullptr
+    const T* ade;        // [3][n] c1, c2, c3, or nullptr
+    const T* pin;        // [2][n] P then J
+    T* pout;
+};
+
+// One work item: strip x chunk.  SRC: the chunk holds source cells.  EXT: 0 no
+// extras, 1 walls and an absorber, 2 a dispersion pole as well.
+template <class IO, int NS, int CPL, bool MU, bool TH, bool SRC, bool UP, int EXT>
 __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T* __restrict__ cl2a,
                                              const typename IO::T* __restrict__ dlnmu, const MarchGeo& g,
                                              const MarchSrc<typename IO::T>& ms,
                                              const AmpPack<typename IO::T, NS>& amps,
-                                             const typename IO::T omega, const bool tau_half, const int strip,
-                                             const int y0, const int segs)
+                                             const typename IO::T omega, const bool tau_half,
+                                             const MarchExt<typename IO::T>& ex, const int strip, const int y0,
+                                             const int segs)
 {
     typedef typename IO::T T;
     constexpr int RING = 4, PF = 2;
@@ -215,8 +236,12 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
         T cl[CPL];
         T dl[MU ? 2 : 1][CPL];
         T sv[CPL];
+        T kp[EXT ? CPL : 1];
+        T co[EXT == 2 ? 5 : 1][CPL];             // c1, c2, c3, P, J
     };
     Row pf[PF];
+    const bool damp = EXT && ex.keep != nullptr, pole = EXT == 2 && ex.ade != nullptr;
+    T kp[EXT ? RING : 1][CPL], co[EXT == 2 ? RING : 1][5][CPL], a4[EXT ? NS : 1][CPL];
     constexpr bool WC = IO::DEV;                 // w0/c^2 is kept per row
     constexpr bool RW = IO::REST;                // and its reciprocal (stored rest codes)
     T cl[RING][CPL], wc[WC ? RING : 1][CPL], rw[RW ? RING : 1][CPL], dl[MU ? RING : 1][2][CPL], sv[SRC ? RING : 1][CPL];
@@ -243,6 +268,21 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                 for (int c = 0; c < CPL; ++c) r.sv[c] = ms.val[(int64_t)seg * (64 * CPL) + lane * CPL + c];
             }
         }
+        if constexpr (EXT) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) r.kp[c] = T(1);
+            if (damp) march_load<T, CPL>(ex.keep + ro, col * (unsigned)sizeof(T), r.kp);
+        }
+        if constexpr (EXT == 2) {
+            if (pole) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    march_load<T, CPL>(ex.ade + (int64_t)k * g.n + ro, col * (unsigned)sizeof(T), r.co[EXT == 2 ? k : 0]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    march_load<T, CPL>(ex.pin + (int64_t)k * g.n + ro, col * (unsigned)sizeof(T), r.co[EXT == 2 ? 3 + k : 0]);
+            }
+        }
         if constexpr (UP) pr = pr == 0 ? ny - 1 : pr - 1;
         else pr = pr + 1 == ny ? 0 : pr + 1;
     };
@@ -266,6 +306,17 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
             }
             if constexpr (SRC) svnew[c] = row.sv[c];
         }
+        T kpnew[CPL], conew[5][CPL];
+        if constexpr (EXT) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                kpnew[c] = row.kp[c];
+                if constexpr (EXT == 2) {
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) conew[k][c] = row.co[EXT == 2 ? k : 0][c];
+                }
+            }
+        }
         if (i + PF < total) fetch(row);
 #pragma unroll
         for (int s = 1; s <= NS; ++s) {
@@ -280,6 +331,28 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                     f[c][UP ? 4 : 2][0] = a2[s - 1][U & 1][c];
                     f[c][UP ? 2 : 4][0] = o[UP ? 2 : 4][c];
                 }
+                if constexpr (EXT != 0) {
+                    if (ex.wx) {
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) {
+                            if (xo + c == 0) f[c][1][0] = ex.nx_ ? -a3[s - 1][c] : a3[s - 1][c];
+                            if (xo + c == nx - 1) f[c][3][0] = ex.nx_ ? -a1[s - 1][c] : a1[s - 1][c];
+                        }
+                    }
+                    if (ex.wy) {
+                        const int y = UP ? y0 + rows - 1 + NS - (i - s) : y0 - NS + (i - s);
+                        if (y == (UP ? ny - 1 : 0)) {
+#pragma unroll
+                            for (int c = 0; c < CPL; ++c)
+                                f[c][UP ? 4 : 2][0] = ex.ny_ ? -a4[s - 1][c] : a4[s - 1][c];
+                        }
+                        if (y == (UP ? 0 : ny - 1)) {
+#pragma unroll
+                            for (int c = 0; c < CPL; ++c)
+                                f[c][UP ? 2 : 4][0] = ex.ny_ ? -a2[s - 1][(U & 1) ^ 1][c] : a2[s - 1][(U & 1) ^ 1][c];
+                        }
+                    }
+                }
             }
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
@@ -287,6 +360,7 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                 a1[s - 1][c] = o[1][c];
                 a3[s - 1][c] = o[3][c];
                 a2[s - 1][U & 1][c] = o[UP ? 4 : 2][c];
+                if constexpr (EXT != 0) a4[EXT ? s - 1 : 0][c] = o[UP ? 2 : 4][c];
             }
             if (s <= LV) {
                 constexpr int R4 = RING;
@@ -321,7 +395,20 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                         }
                     } else {
                         T out[5][1];
+                        if constexpr (EXT == 2) {
+                            T (&e)[5][CPL] = co[EXT == 2 ? q : 0];
+                            if (pole) ade_advance<T>(e[0][c], e[1][c], e[2][c], cl[q][c], rho[0], e[3][c], e[4][c]);
+                        }
                         collide<2, T>(f[c], cl[q][c], Sp, SRC || MU, omega, TH || tau_half, rho, K, out);
+                        if constexpr (EXT == 2) {
+                            if (pole) out[0][0] += co[EXT == 2 ? q : 0][4][c] / cl[q][c];
+                        }
+                        if constexpr (EXT != 0) {
+                            if (damp) {
+#pragma unroll
+                                for (int k = 0; k < 5; ++k) out[k][0] *= kp[EXT ? q : 0][c];
+                            }
+                        }
 #pragma unroll
                         for (int k = 0; k < 5; ++k) {
                             if (s == NS) st.v[k][c] = out[k][0];
@@ -333,6 +420,14 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                     unsigned xc = (unsigned)xo;
                     asm volatile("" : "+v"(xc));
                     io.store(st, orow, xc);
+                    if constexpr (EXT == 2) {
+                        if (pole) {
+#pragma unroll
+                            for (int k = 0; k < 2; ++k)
+                                march_store<T, CPL>(ex.pout + (int64_t)k * g.n + orow, xc * (unsigned)sizeof(T),
+                                                    co[EXT == 2 ? q : 0][3 + k]);
+                        }
+                    }
                 }
             }
         }
@@ -347,6 +442,11 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                 dl[MU ? U : 0][1][c] = dlnew[1][c];
             }
             if constexpr (SRC) sv[SRC ? U : 0][c] = svnew[c];
+            if constexpr (EXT != 0) kp[EXT ? U : 0][c] = kpnew[c];
+            if constexpr (EXT == 2) {
+#pragma unroll
+                for (int k = 0; k < 5; ++k) co[EXT == 2 ? U : 0][k][c] = conew[k][c];
+            }
         }
     };
 #define LBEM_IC(v) std::integral_constant<int, (v)>{}
@@ -380,12 +480,13 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
 }
 
 // Work item w (uniform over the wave).
-template <class IO, int NS, int CPL, bool MU, bool TH>
+template <class IO, int NS, int CPL, bool MU, bool TH, int EXT = 0>
 __device__ __forceinline__ void march2d_work(const IO& io, const typename IO::T* __restrict__ cl2a,
                                              const typename IO::T* __restrict__ dlnmu, const MarchGeo& g,
                                              const MarchSrc<typename IO::T>& ms,
                                              const AmpPack<typename IO::T, NS>& amps,
-                                             const typename IO::T omega, const bool tau_half, const int w)
+                                             const typename IO::T omega, const bool tau_half, const int w,
+                                             const MarchExt<typename IO::T>& ex = MarchExt<typename IO::T>{})
 {
     const int strip = w % g.strips, y0 = (w / g.strips) * g.rows;
     unsigned m = 0;
@@ -405,24 +506,25 @@ __device__ __forceinline__ void march2d_work(const IO& io, const typename IO::T*
     }
     const bool up = (w / g.strips) & 1;
     if (src)
-        march2d_item<IO, NS, CPL, MU, TH, true, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
+        march2d_item<IO, NS, CPL, MU, TH, true, false, EXT>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, ex, strip, y0, segs);
     else if (up)
-        march2d_item<IO, NS, CPL, MU, TH, false, true>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
+        march2d_item<IO, NS, CPL, MU, TH, false, true, EXT>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, ex, strip, y0, segs);
     else
-        march2d_item<IO, NS, CPL, MU, TH, false, false>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, strip, y0, segs);
+        march2d_item<IO, NS, CPL, MU, TH, false, false, EXT>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half, ex, strip, y0, segs);
 }
 
-template <class IO, int NS, int CPL, bool MU, bool TH>
+template <class IO, int NS, int CPL, bool MU, bool TH, int EXT = 0>
 __global__ __launch_bounds__(NT) void k_march2d(const IO io, const typename IO::T* __restrict__ cl2a,
                                                const typename IO::T* __restrict__ dlnmu, const MarchGeo g,
                                                const MarchSrc<typename IO::T> ms,
                                                const AmpPack<typename IO::T, NS> amps,
-                                               const typename IO::T omega, const int tau_half)
+                                               const typename IO::T omega, const int tau_half,
+                                               const MarchExt<typename IO::T> ex)
 {
     const int b = remap_block(blockIdx.x, g.nblocks, 1);
     const int w = __builtin_amdgcn_readfirstlane(b * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6));
     if (w >= g.nwork) return;
-    march2d_work<IO, NS, CPL, MU, TH>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, w);
+    march2d_work<IO, NS, CPL, MU, TH, EXT>(io, cl2a, dlnmu, g, ms, amps, omega, tau_half != 0, w, ex);
 }
 
 }  // namespace lbem
