@@ -217,7 +217,7 @@ def run_workload(name: str, prec: str, steps: int, warmup: int, streaming: str =
 
 # the headline: config 4 with FP16 deviation storage in ghost coordinates
 PRIMARY_PREC = "f16ghost"
-PRIMARY_KERNEL = "k_step_dev3r<__half,ghost,mu=0,nts=1,cx=2,512,ext=0>"
+PRIMARY_KERNEL = "k_pair_dev3<__half,ghost,mu=0>"
 PRIMARY_TRAFFIC = "c4_512_f16ghost"
 CPU_SAMPLE_CROP = 128
 
@@ -491,8 +491,7 @@ def main():
                 r = run_workload(name, prec, k, w, st, p=make_problem(name, nprob if name == "c4" else 1100))
                 if name == "c2":
                     r["note"] = ("2048^2 state (101-185 MB) fits the 256 MB Infinity Cache: not an HBM point; "
-                                 "the FP32 pull default runs four steps per launch and is bound by vector-ALU "
-                                 "issue (0.69 of the VALU issue slots, profiles/k_step_stream_collide.md)")
+                                 "the FP32 pull default runs four steps per launch in registers (k_march2d)")
                 variants.append(r)
             except Exception as e:  # report, do not hide
                 variants.append(dict(workload=name, prec=prec, streaming=st, error=str(e)))
@@ -513,9 +512,9 @@ def main():
         print("[bench] cpu baseline (oracle)", file=sys.stderr, flush=True)
         cpu = cpu_baseline(CPU_SAMPLE_CROP)
 
-    # one launch = one time step of the whole lattice: the kernel reads the
+    # one launch = spl time steps of the whole lattice: the kernel reads the
     # stored state (FP32 moments + 15 FP16 ghost codes per cell) and c_L^2 once
-    # and writes the new state once, 112 B per cell update
+    # and writes the new state once, 112 B per cell and launch
     spl = prim["steps_per_launch"]
     launch_us = prim["avg_launch_us"] * spl
     achieved = prim["bytes_per_cell"] * p.n / (launch_us * 1e-6) / 1e9
@@ -543,8 +542,9 @@ def main():
                      "kernel": PRIMARY_KERNEL, "steps_per_launch": spl, "avg_launch_us": launch_us,
                      "bytes_per_cell_per_launch": prim["bytes_per_cell"], "cells_per_launch": p.n,
                      "bytes_per_cell_update": prim["bytes_per_cell"] / spl,
-                     "note": "algorithmic bytes (section 8(d)): 2 x (6 x 4 B moments + 15 x 2 B codes) + 4 B c_L^2 "
-                             "per cell update; event-timed over the timed steps on the launch stream"},
+                     "note": "algorithmic bytes: 2 x (6 x 4 B moments + 15 x 2 B codes) + 4 B c_L^2 per cell and "
+                             "launch of steps_per_launch time steps; event-timed over the timed steps on the "
+                             "launch stream"},
         "cpu_baseline": cpu,
         "hbm_frac": prim["hbm_frac"],
         "finite": prim["finite"],
