@@ -50,7 +50,7 @@ __global__ __launch_bounds__(1024, 4) void k_batch_pair3d(const BatchHdr* __rest
     const int s = (G.cur0 + 1 + j) & 1;
     const PairGeo g = G.pgeo;
     const int t = b - G.multi_base, tx = t % g.tiles_x, r = t / g.tiles_x;
-    const int y0 = (r % g.tiles_y) * PRY, z0 = (r / g.tiles_y) * g.lz;
+    const int y0 = (r % g.tiles_y) * g.sy, z0 = (r / g.tiles_y) * g.lz;
     const PairSrc ps{nullptr, gmem<const int>(G.psrc_idx), gmem<const float>(G.psrc_val), G.psrc_pair};
     AmpPack<float, 2> a;
 #pragma unroll

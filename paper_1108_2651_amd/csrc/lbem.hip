@@ -110,6 +110,8 @@ static void make_pair_geo(lbem_s* h)
     g.nx = (int)h->cfg.nx; g.ny = (int)h->cfg.ny; g.nz = (int)h->cfg.nz; g.n = h->n;
     g.tiles_x = (g.nx + PRX - 1) / PRX;
     g.tiles_y = (g.ny + PRY - 1) / PRY;
+    g.sx = (g.nx + g.tiles_x - 1) / g.tiles_x;      // even tiles: no lane loads for another
+    g.sy = (g.ny + g.tiles_y - 1) / g.tiles_y;
     const int64_t cus = device_cus(), cols = (int64_t)g.tiles_x * g.tiles_y;
     g.lz = std::max(1, env_int("LBEM_FUSE3_LZ", march_planes(cols, g.nz, cus, 4)));
     g.nblocks = (int)(cols * ((g.nz + g.lz - 1) / g.lz));
@@ -779,7 +781,7 @@ static int build_pair_source(lbem_s* h, const std::vector<std::pair<int64_t, dou
 {
     const PairGeo& g = h->pgeo;
     const bool f32 = h->prec == LBEM_F32;
-    const int tw = f32 ? g.sx : PRX, th = f32 ? g.sy : PRY, halo = f32 ? 1 : 2, len = f32 ? PFSEG : 64;
+    const int tw = g.sx, th = g.sy, halo = f32 ? 1 : 2, len = f32 ? PFSEG : 64;
     const size_t plane = (size_t)g.ny * g.nz;
     std::vector<int> idx((size_t)g.tiles_x * plane, -1);
     std::vector<unsigned char> flag((size_t)g.nblocks, 0);

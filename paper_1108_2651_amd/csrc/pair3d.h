@@ -9,8 +9,11 @@
 // (+-x cross lanes by DPP wave shifts), +z for two planes, -z is handed over in
 // the same iteration, and +-y go through LDS, two buffers, one barrier per
 // plane.  The two outer columns and rows on each side are recomputed by the
-// neighbouring tiles: 60 x 12 cells are stored; the outermost rows load and
-// decode only what their +-y populations need.  The arithmetic is the
+// neighbouring tiles: up to 60 x 12 cells are stored, the lattice cut into even
+// tiles (with full tiles and a rest the lanes of the last one load again what
+// others hold: ten steps of FP16 ghost 512^3 26.9 ms, even tiles of 57 x 12
+// 25.2); the outermost rows load and decode only what their +-y populations
+// need.  The arithmetic is the
 // single-step kernels', so two single steps and one launch give the same bits.
 //
 // Why this shape: the persistent state of a cell between planes is 40 floats,
@@ -44,7 +47,7 @@ __device__ __forceinline__ const T& at32(const T* base, unsigned idx)
     return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + idx * (unsigned)sizeof(T));
 }
 
-constexpr int PRX = 60, PRY = 12;        // stored columns and rows of a tile (64 lanes x 16 waves)
+constexpr int PRX = 60, PRY = 12;        // most columns and rows that a tile stores (64 lanes x 16 waves)
 
 struct PairSrc {
     const unsigned char* flag;           // per block: some row it updates holds source cells (nullptr: no source)
@@ -81,33 +84,36 @@ __device__ __forceinline__ void pair_march(const float* Min, const H* Din, float
     constexpr bool RW = !GH;             // the reciprocal of w0/c^2 is kept for the rest codes
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int tid = threadIdx.x;
-    const int x0 = tx * PRX;
+    const int x0 = tx * g.sx;
     const int planes = min(g.lz, g.nz - z0);
     auto wrap = [](int v, int m) { v %= m; return v < 0 ? v + m : v; };
     const unsigned col0 = (unsigned)wrap(x0 - 2 + lane, g.nx);
     const int gy = wrap(y0 - 2 + w, g.ny);
     const int64_t nxy = (int64_t)g.nx * g.ny, rowo = (int64_t)gy * g.nx;
-    const bool edge = w == 0 || w == 15;               // rows decoded for their +y / -y populations only
-    const bool inner = w >= 2 && w < 2 + PRY;          // rows that take both steps and are stored
-    const bool keep = inner && lane >= 2 && lane < 2 + PRX && x0 - 2 + lane < g.nx && y0 - 2 + w < g.ny;
+    const bool live = w < g.sy + 4, col = lane < g.sx + 4;   // the tile and its halo
+    const bool edge = w == 0 || w >= g.sy + 3;         // rows decoded for their +y / -y populations only
+    const bool inner = w >= 2 && w < 2 + g.sy;         // rows that take both steps and are stored
+    const bool keep = inner && lane >= 2 && lane < 2 + g.sx && x0 - 2 + lane < g.nx && y0 - 2 + w < g.ny;
 
-    float m[NM], cl = 1.f, sv = 0.f;
+    float m[NM] = {}, cl = 1.f, sv = 0.f;
     H cd[NC] = {};
     int gz = wrap(z0 - 2, g.nz);
     auto fetch = [&]() {
         const int64_t o = (int64_t)gz * nxy + rowo;
-        unsigned col = col0;
-        asm volatile("" : "+v"(col));
+        if (col) {
+            unsigned c = col0;
+            asm volatile("" : "+v"(c));
 #pragma unroll
-        for (int t = 0; t < NM; ++t) m[t] = at32(Min + (int64_t)t * g.n + o, col);
-#pragma unroll
-        for (int s = 0; s < NC; ++s)
-            if (pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
-        if (!edge) {
+            for (int t = 0; t < NM; ++t) m[t] = at32(Min + (int64_t)t * g.n + o, c);
 #pragma unroll
             for (int s = 0; s < NC; ++s)
-                if (!pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
-            cl = at32(cl2a + o, col);
+                if (pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, c);
+            if (!edge) {
+#pragma unroll
+                for (int s = 0; s < NC; ++s)
+                    if (!pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, c);
+                cl = at32(cl2a + o, c);
+            }
         }
         if constexpr (SRC) {
             const int seg = ps.idx[((int64_t)tx * g.nz + gz) * g.ny + gy];
@@ -185,8 +191,10 @@ __device__ __forceinline__ void pair_march(const float* Min, const H* Din, float
         Left N0 = L0, N1 = L1;
         float mz0[P], mz1[P];
         const float cl0 = cl, sv0 = sv, wc0 = 1.f / cl0 - float(D);
-        spread(m, cd, wc0, ly[bw][0], !edge, N0, mz0);
-        if (it + 1 < planes + 4) fetch();
+        if (live) {
+            spread(m, cd, wc0, ly[bw][0], !edge, N0, mz0);
+            if (it + 1 < planes + 4) fetch();
+        }
         if (it >= 2 && !edge) {
             float M[NM];
             H code[NC];
@@ -236,10 +244,10 @@ __global__ __launch_bounds__(1024, 4) void k_pair_dev3(const float* Min, const H
     const int tx = b % g.tiles_x, r = b / g.tiles_x;
     const int ty = r % g.tiles_y, zc = r / g.tiles_y;
     if (ps.flag != nullptr && ps.flag[b] != 0)
-        pair_march<H, GH, MU, true>(Min, Din, Mout, Dout, cl2a, dlnmu, g, ps, amps, omega, tau_half != 0, tx, ty * PRY,
+        pair_march<H, GH, MU, true>(Min, Din, Mout, Dout, cl2a, dlnmu, g, ps, amps, omega, tau_half != 0, tx, ty * g.sy,
                                     zc * g.lz, ly);
     else
-        pair_march<H, GH, MU, false>(Min, Din, Mout, Dout, cl2a, dlnmu, g, ps, amps, omega, tau_half != 0, tx, ty * PRY,
+        pair_march<H, GH, MU, false>(Min, Din, Mout, Dout, cl2a, dlnmu, g, ps, amps, omega, tau_half != 0, tx, ty * g.sy,
                                      zc * g.lz, ly);
 }
 
