@@ -139,6 +139,8 @@ static void make_pair_geo(lbem_s* h)
     f = g;
     f.tiles_x = (f.nx + FLX - 1) / FLX;
     f.tiles_y = (f.ny + FLY - 1) / FLY;
+    f.sx = (f.nx + f.tiles_x - 1) / f.tiles_x;
+    f.sy = (f.ny + f.tiles_y - 1) / f.tiles_y;
     f.lz = march_planes((int64_t)f.tiles_x * f.tiles_y, f.nz, cus, 2);
     f.xcd = std::max(2, f.tiles_x);
     f.nblocks = env_int("LBEM_FIELDS3", share >= 0.27) ? f.tiles_x * f.tiles_y * ((f.nz + f.lz - 1) / f.lz) : 0;

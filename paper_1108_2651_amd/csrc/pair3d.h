@@ -253,8 +253,8 @@ __global__ __launch_bounds__(1024, 4) void k_pair_dev3(const float* Min, const H
 
 // E and B of a 3D 16-bit state not yet streamed, on the tiles of the march
 // above with one level: every stored cell is decoded once (the per-cell reader
-// decodes each arrival from its neighbour's moments and codes), 62 x 14 cells
-// of a tile are written.  Same arithmetic as k_fields, so the same bits.
+// decodes each arrival from its neighbour's moments and codes), up to 62 x 14 cells
+// of a tile are written, even tiles.  Same arithmetic as k_fields, so the same bits.
 // Bound by memory, 58 B read and 48 B written per cell (FP16 ghost): 256^3 792
 // -> 491 us per call (3.6 TB/s), 512^3 6.4 -> 3.6 ms.
 constexpr int FLX = 62, FLY = 14;
@@ -270,36 +270,39 @@ __global__ __launch_bounds__(1024, 4) void k_fields_dev3(const float* Min, const
     const int ty = r % g.tiles_y, zc = r / g.tiles_y;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int tid = threadIdx.x;
-    const int x0 = tx * FLX, y0 = ty * FLY, z0 = zc * g.lz;
+    const int x0 = tx * g.sx, y0 = ty * g.sy, z0 = zc * g.lz;
     const int planes = min(g.lz, g.nz - z0);
     auto wrap = [](int v, int m) { v %= m; return v < 0 ? v + m : v; };
     const unsigned col0 = (unsigned)wrap(x0 - 1 + lane, g.nx);
     const int64_t nxy = (int64_t)g.nx * g.ny, rowo = (int64_t)wrap(y0 - 1 + w, g.ny) * g.nx;
-    const bool edge = w == 0 || w == 15;               // rows decoded for their +y / -y populations only
-    const bool keep = !edge && lane >= 1 && lane < 1 + FLX && x0 - 1 + lane < g.nx && y0 - 1 + w < g.ny;
+    const bool live = w < g.sy + 2, col = lane < g.sx + 2;   // the tile and its halo
+    const bool edge = w == 0 || w >= g.sy + 1;         // rows decoded for their +y / -y populations only
+    const bool keep = !edge && lane >= 1 && lane < 1 + g.sx && x0 - 1 + lane < g.nx && y0 - 1 + w < g.ny;
 
-    float m[NM], cl = 1.f;
+    float m[NM] = {}, cl = 1.f;
     H cd[NC] = {};
     int gz = wrap(z0 - 1, g.nz);
     auto fetch = [&]() {
         const int64_t o = (int64_t)gz * nxy + rowo;
-        unsigned col = col0;
-        asm volatile("" : "+v"(col));
+        if (col) {
+            unsigned c = col0;
+            asm volatile("" : "+v"(c));
 #pragma unroll
-        for (int t = 0; t < NM; ++t) m[t] = at32(Min + (int64_t)t * g.n + o, col);
-#pragma unroll
-        for (int s = 0; s < NC; ++s)
-            if (pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
-        if (!edge) {
+            for (int t = 0; t < NM; ++t) m[t] = at32(Min + (int64_t)t * g.n + o, c);
 #pragma unroll
             for (int s = 0; s < NC; ++s)
-                if (!pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, col);
-            cl = at32(cl2a + o, col);
+                if (pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, c);
+            if (!edge) {
+#pragma unroll
+                for (int s = 0; s < NC; ++s)
+                    if (!pair_edge_code<GH>(s)) cd[s] = at32(Din + (int64_t)s * g.n + o, c);
+                cl = at32(cl2a + o, c);
+            }
         }
         gz = gz + 1 == g.nz ? 0 : gz + 1;
     };
     float rest[P] = {}, px[P] = {}, mx[P] = {}, pz[P] = {}, pzo[P] = {}, clp = 1.f;   // of the plane before
-    fetch();
+    if (live) fetch();
     for (int it = 0; it < planes + 2; ++it) {
         const int bw = it & 1, br = bw ^ 1;
         const float wc0 = 1.f / cl - float(D), sc = row_scale(m), cl0 = cl;
@@ -317,7 +320,7 @@ __global__ __launch_bounds__(1024, 4) void k_fields_dev3(const float* Min, const
             npz[p] = row_pop<GH>(m, get, sc, wc0, 3, p);
             mz[p] = row_pop<GH>(m, get, sc, wc0, 6, p);
         }
-        if (it + 1 < planes + 2) fetch();
+        if (live && it + 1 < planes + 2) fetch();
         if (it >= 2 && !edge) {
             double f[Q][P];
 #pragma unroll
