@@ -20,15 +20,15 @@
 // so one cell per thread and 1024 threads fill the registers of a CU (118-128
 // of 128 VGPRs); a narrower or lower tile recomputes and re-reads more.  What
 // bounds it: L1 -> L2 requests (0.12 per cycle and CU, the rate of every 3D
-// kernel here): 154 of them per 64 stored cells and two steps, against about
-// 100 per step of the row tiles, and counted traffic of 167 B per cell and two
-// steps against 253.  Without memory (every plane the same) a launch at 512^3
-// takes 2.7 of its 4.4 ms.  Stores are plain: the partial lines at tile edges
-// merge in L2 (streaming stores ran 5.7 against 4.4 ms).  Tiles are dealt to
+// kernel here) and bytes: counted traffic of 147 B per cell and two steps at
+// 512^3, 4.63 TB/s, the rate of a large copy, against 254 B of two single
+// steps.  Without memory (every plane the same) a launch there takes 2.7 of its
+// 4.27 ms.  Stores are plain: the partial lines at tile edges
+// merge in L2 (streaming stores ran 5.7 against 4.4 ms, on full tiles).  Tiles are dealt to
 // the XCDs in runs of one row of tiles, which share their x-halo lines (512^3,
 // us per launch, runs of 0 / 1 / 3 / 9 tiles: 5350 / 5340 / 4810 / 4360).
 // Measured, us per step, row tiles (one step per launch) -> this kernel: FP16
-// ghost 512^3 2920 -> 2300, 256^3 370 -> 316, 160^3 105 -> 72, 250x190x171 274
+// ghost 512^3 2890 -> 2135, 256^3 370 -> 316, 160^3 105 -> 72, 250x190x171 274
 // -> 133; FP16-dev 256^3 438 -> 374, 250x190x171 358 -> 163.
 #pragma once
 #include "march2d.h"
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(1024, 4) void k_pair_dev3(const float* Min, const H
 // decodes each arrival from its neighbour's moments and codes), up to 62 x 14 cells
 // of a tile are written, even tiles.  Same arithmetic as k_fields, so the same bits.
 // Bound by memory, 58 B read and 48 B written per cell (FP16 ghost): 256^3 792
-// -> 491 us per call (3.6 TB/s), 512^3 6.4 -> 3.6 ms.
+// -> 491 us per call (3.6 TB/s), 512^3 6.4 -> 3.4 ms.
 constexpr int FLX = 62, FLY = 14;
 
 template <typename H, bool GH>
