@@ -87,7 +87,7 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in ("paper_1108_2651_amd/csrc/kernels.h", "paper_1108_2651_amd/csrc/march2d.h",
               "paper_1108_2651_amd/csrc/pair3d.h", "paper_1108_2651_amd/csrc/pair3f.h", "paper_1108_2651_amd/csrc/batch_multi.h",
-              "paper_1108_2651_amd/csrc/lattice.h", "paper_1108_2651_amd/csrc/impl.h",
+              "paper_1108_2651_amd/csrc/lattice.h", "paper_1108_2651_amd/csrc/limits.h", "paper_1108_2651_amd/csrc/impl.h",
               "paper_1108_2651_amd/csrc/impl.hip", "paper_1108_2651_amd/csrc/lbem.hip"):
         h.update(_code_only(open(os.path.join(ROOT, f), encoding="utf-8").read()).encode())
     h.update(open(os.path.join(ROOT, "paper_1108_2651_amd/build.py"), "rb").read())

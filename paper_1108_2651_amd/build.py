@@ -13,7 +13,7 @@ LIB = os.path.join(OUT_DIR, "liblbem.so")
 # (source, extra flags) of each translation unit, compiled in parallel
 UNITS = [("lbem.hip", [])] + [("impl.hip", [f"-DLBEM_UNIT={k}"]) for k in range(5)]
 SOURCES = [os.path.join(CSRC, f) for f in ("lbem.hip", "impl.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("impl.h", "kernels.h", "march2d.h", "pair3d.h", "pair3f.h", "batch_multi.h", "lattice.h")] + [
+HEADERS = [os.path.join(CSRC, f) for f in ("impl.h", "kernels.h", "march2d.h", "pair3d.h", "pair3f.h", "batch_multi.h", "lattice.h", "limits.h")] + [
     os.path.join(os.path.dirname(HERE), "include", "lbem.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -14,6 +14,7 @@
 
 #include "../../include/lbem.h"
 #include "kernels.h"
+#include "limits.h"
 #include "march2d.h"
 #include "pair3d.h"
 #include "pair3f.h"
@@ -428,6 +429,14 @@ static hipError_t go_fused(lbem_s* h, const T* src, T* dst, const double* amp, i
 {
     if constexpr (sizeof(T) == 4) {
         if (h->mcpl == 2) return go_fused_c<T, 2>(h, src, dst, amp, ns);
+    } else if (!offsets32(h->cfg.nx, sizeof(T))) {
+        // launches of two without extras (make_fused_geo)
+        typedef MarchPlain<T, 1, true> IO;
+        const IO io{src, dst, h->n};
+        if (ns != 2 || has_bx(h)) return hipErrorInvalidValue;
+        if (h->mu_set) launch_march<IO, 2, 1, true, false>(h, io, amp);
+        else launch_march<IO, 2, 1, false, false>(h, io, amp);
+        return hipGetLastError();
     }
     return go_fused_c<T, 1>(h, src, dst, amp, ns);
 }

@@ -230,10 +230,16 @@ static void make_fused_geo(lbem_s* h)
     // or without a varying mu (the bytes per update fall with the steps and
     // nothing else grows); calls for fewer steps take the launches of two and
     // three.
-    const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
+    const int nx = (int)h->cfg.nx;
     h->fuse_ns = env_int("LBEM_FUSE", 4);
     if (h->fuse_ns < 1 || h->fuse_ns > 4) h->fuse_ns = 1;
     h->ext_ns = h->prec <= LBEM_F32 && h->n >= 4096 ? (h->fuse_ns >= 4 ? 4 : (h->fuse_ns >= 2 ? 2 : 1)) : 1;
+    // FP64 rows longer than 2^29 columns need 64-bit offsets within a row: two steps
+    // per launch, single steps with extras.
+    if (!offsets32(nx, h->prec == LBEM_F64 ? 8 : 4)) {
+        h->fuse_ns = std::min(h->fuse_ns, 2);
+        h->ext_ns = 1;
+    }
     // FP32 lattices of 8e6 cells and more, rows of even length: two cells per
     // lane.  One eighth of the columns is recomputed with one cell per lane,
     // one sixteenth with two, which shows once the state streams from HBM (us

@@ -74,11 +74,12 @@ struct MarchSrc {
 };
 
 // CPL neighbouring elements at a byte offset off a scalar base.  A pair (FP32)
-// moves as one 8-byte access, aligned to 4 bytes.
+// moves as one 8-byte access, aligned to 4 bytes.  The offset within a row has 32
+// bits where every row fits them (offsets32), as all FP32 rows do.
 typedef float MarchPair __attribute__((ext_vector_type(2)));
 typedef MarchPair MarchPairU __attribute__((aligned(4)));
-template <typename S, int CPL>
-__device__ __forceinline__ void march_load(const S* base, unsigned off, S (&v)[CPL])
+template <typename S, int CPL, typename Off>
+__device__ __forceinline__ void march_load(const S* base, Off off, S (&v)[CPL])
 {
     const char* p = reinterpret_cast<const char*>(base) + off;
     if constexpr (CPL == 1) {
@@ -90,8 +91,8 @@ __device__ __forceinline__ void march_load(const S* base, unsigned off, S (&v)[C
         v[1] = w[1];
     }
 }
-template <typename S, int CPL>
-__device__ __forceinline__ void march_store(S* base, unsigned off, const S (&v)[CPL])
+template <typename S, int CPL, typename Off>
+__device__ __forceinline__ void march_store(S* base, Off off, const S (&v)[CPL])
 {
     char* p = reinterpret_cast<char*>(base) + off;
     if constexpr (CPL == 1) {
@@ -103,10 +104,12 @@ __device__ __forceinline__ void march_store(S* base, unsigned off, const S (&v)[
     }
 }
 
-// storage of the plain formats: five populations of type T per cell
-template <typename T_, int CPL>
+// storage of the plain formats: five populations of type T per cell.  WIDE:
+// 64-bit offsets within a row.
+template <typename T_, int CPL, bool WIDE = false>
 struct MarchPlain {
     typedef T_ T;
+    typedef typename std::conditional<WIDE, size_t, unsigned>::type Off;
     const T* src;
     T* dst;
     int64_t n;
@@ -115,7 +118,7 @@ struct MarchPlain {
     __device__ __forceinline__ void load(Raw& r, int64_t row, unsigned col) const
     {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) march_load<T, CPL>(src + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
+        for (int k = 0; k < 5; ++k) march_load<T, CPL>(src + (int64_t)k * n + row, (Off)col * (Off)sizeof(T), r.v[k]);
     }
     __device__ __forceinline__ void decode(const Raw& r, const T (&)[CPL], T (&o)[5][CPL]) const
     {
@@ -128,7 +131,7 @@ struct MarchPlain {
     {
 #pragma unroll
         for (int k = 0; k < 5; ++k)
-            march_store<T, CPL>(dst + (int64_t)k * n + row, col * (unsigned)sizeof(T), r.v[k]);
+            march_store<T, CPL>(dst + (int64_t)k * n + row, (Off)col * (Off)sizeof(T), r.v[k]);
     }
 };
 
@@ -136,6 +139,7 @@ struct MarchPlain {
 template <typename H, bool GH, int CPL>
 struct MarchDev {
     typedef float T;
+    typedef unsigned Off;
     typedef H Code;
     static constexpr bool GHOST = GH;
     static constexpr int NC = DevSlots<2, GH>::N;
@@ -214,6 +218,7 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                                              const int segs)
 {
     typedef typename IO::T T;
+    typedef typename IO::Off Off;
     constexpr int RING = 4, PF = 2;
     static_assert(NS <= RING && NS <= MARCH_HX && RING % PF == 0, "ring indices repeat every RING rows");
     constexpr int HX = MARCH_HX, OW = 64 * CPL - 2 * HX;
@@ -253,10 +258,10 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
         unsigned col = col0;
         asm volatile("" : "+v"(col));            // keeps the 32-bit offset next to its loads (scalar-base form)
         io.load(r.raw, ro, col);
-        march_load<T, CPL>(cl2a + ro, col * (unsigned)sizeof(T), r.cl);
+        march_load<T, CPL>(cl2a + ro, (Off)col * (Off)sizeof(T), r.cl);
         if constexpr (MU) {
-            march_load<T, CPL>(dlnmu + ro, col * (unsigned)sizeof(T), r.dl[0]);
-            march_load<T, CPL>(dlnmu + g.n + ro, col * (unsigned)sizeof(T), r.dl[MU ? 1 : 0]);
+            march_load<T, CPL>(dlnmu + ro, (Off)col * (Off)sizeof(T), r.dl[0]);
+            march_load<T, CPL>(dlnmu + g.n + ro, (Off)col * (Off)sizeof(T), r.dl[MU ? 1 : 0]);
         }
         if constexpr (SRC) {
             const int seg = __builtin_amdgcn_readlane(segs, nf);   // lane k holds the segment of input row k
@@ -271,16 +276,16 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
         if constexpr (EXT) {
 #pragma unroll
             for (int c = 0; c < CPL; ++c) r.kp[c] = T(1);
-            if (damp) march_load<T, CPL>(ex.keep + ro, col * (unsigned)sizeof(T), r.kp);
+            if (damp) march_load<T, CPL>(ex.keep + ro, (Off)col * (Off)sizeof(T), r.kp);
         }
         if constexpr (EXT == 2) {
             if (pole) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
-                    march_load<T, CPL>(ex.ade + (int64_t)k * g.n + ro, col * (unsigned)sizeof(T), r.co[EXT == 2 ? k : 0]);
+                    march_load<T, CPL>(ex.ade + (int64_t)k * g.n + ro, (Off)col * (Off)sizeof(T), r.co[EXT == 2 ? k : 0]);
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
-                    march_load<T, CPL>(ex.pin + (int64_t)k * g.n + ro, col * (unsigned)sizeof(T), r.co[EXT == 2 ? 3 + k : 0]);
+                    march_load<T, CPL>(ex.pin + (int64_t)k * g.n + ro, (Off)col * (Off)sizeof(T), r.co[EXT == 2 ? 3 + k : 0]);
             }
         }
         if constexpr (UP) pr = pr == 0 ? ny - 1 : pr - 1;
@@ -424,7 +429,7 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                         if (pole) {
 #pragma unroll
                             for (int k = 0; k < 2; ++k)
-                                march_store<T, CPL>(ex.pout + (int64_t)k * g.n + orow, xc * (unsigned)sizeof(T),
+                                march_store<T, CPL>(ex.pout + (int64_t)k * g.n + orow, (Off)xc * (Off)sizeof(T),
                                                     co[EXT == 2 ? q : 0][3 + k]);
                         }
                     }
