@@ -143,7 +143,8 @@ static void make_pair_geo(lbem_s* h)
     f.sy = (f.ny + f.tiles_y - 1) / f.tiles_y;
     f.lz = march_planes((int64_t)f.tiles_x * f.tiles_y, f.nz, cus, 2);
     f.xcd = std::max(2, f.tiles_x);
-    f.nblocks = env_int("LBEM_FIELDS3", share >= 0.27) ? f.tiles_x * f.tiles_y * ((f.nz + f.lz - 1) / f.lz) : 0;
+    const bool fits = offsets32(f.nx, 8);           // it writes doubles at 32-bit offsets within a row
+    f.nblocks = fits && env_int("LBEM_FIELDS3", share >= 0.27) ? f.tiles_x * f.tiles_y * ((f.nz + f.lz - 1) / f.lz) : 0;
 }
 
 // Two steps per launch for 3D FP32 on the tiles of k_pair_f32, up to 64 x 13

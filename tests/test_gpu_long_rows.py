@@ -1,6 +1,9 @@
-"""2D FP64 rows of more than 2^29 columns, whose byte offsets within a row need 64
-bits: two steps per launch against the FP64 oracle on windows around pulses and
-source cells on both sides of column 2^29, and no field elsewhere."""
+"""Rows of more than 2^29 columns, whose byte offsets of doubles need 64 bits.  2D
+FP64: two steps per launch against the FP64 oracle on windows around pulses and
+source cells on both sides of column 2^29, and no field elsewhere.  3D 16-bit: the
+fields as the per-cell reader gives them, also where the tiled reader is asked for."""
+import os
+
 import numpy as np
 import pytest
 
@@ -62,6 +65,45 @@ def test_long_rows(mu):
         seen += int(torch.count_nonzero(Eg[2][at]))
         assert int(torch.count_nonzero(Eg[2][at])) > 0, c
     assert int(torch.count_nonzero(Eg[2])) == seen
+    s.close()
+    del s, Eg, Bg
+    torch.cuda.empty_cache()
+
+
+def test_fields_of_long_rows():
+    import torch
+    torch.cuda.empty_cache()
+    n = 2 ** 29 + 192
+    E, B = np.zeros((3, n)), np.zeros((3, n))
+    centres = [0, 40, 2 ** 28, 2 ** 29 - 20, 2 ** 29, 2 ** 29 + 20, n - 40]
+    for k, c in enumerate(centres):
+        E[:, c], B[:, c] = (1.0, -0.5, 0.25 + k), (0.5, 0.125, -k)
+    os.environ["LBEM_FIELDS3"] = "1"
+    try:
+        s = lbem.Solver(3, (n, 1, 1), "f16ghost")
+    finally:
+        os.environ.pop("LBEM_FIELDS3", None)
+    announce(f"fields 3d f16ghost {n}x1x1: set-up")
+    s.set_medium(np.full(n, 1.0))
+    s.init_fields(E, B)
+    announce("  step")
+    s.step(1)
+    Eg = torch.zeros((3, n), dtype=torch.float64, device="cuda")
+    Bg = torch.zeros_like(Eg)
+    s.moments_device(Eg, Bg)
+    seen = [0] * 6
+    for c in centres:
+        idx = np.arange(c - H, c + H + 1) % n
+        o = O.Oracle(3, (2 * H + 1, 1, 1))
+        o.set_medium(np.full(2 * H + 1, 1.0))
+        o.init_fields(E[:, idx], B[:, idx])
+        o.step(1)
+        at = torch.from_numpy(idx).cuda()
+        for k, (got, want) in enumerate(zip((*Eg, *Bg), (*o.fields()[0], *o.fields()[1]))):
+            got = got[at].cpu().numpy()
+            assert np.abs(got - want).max() <= TOL["f16ghost"] * np.abs(o.fields()).max(), (c, k)
+            seen[k] += np.count_nonzero(got)
+    assert [int(torch.count_nonzero(f)) for f in (*Eg, *Bg)] == seen
     s.close()
     del s, Eg, Bg
     torch.cuda.empty_cache()
