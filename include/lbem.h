@@ -153,9 +153,12 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
  * FP64, and with walls in 2D FP32 and FP64; elsewhere these, and anisotropy
  * everywhere, make every launch a single step.  The result does not depend on
  * this choice (bit for bit).  The state moves to its other copy with every
- * launch; under stream capture launches are chosen so that a graph of an even
- * number of steps of a handle that has taken a step ends in the copy that it
- * began with, and can be replayed. */
+ * launch.  A captured call takes launches by which the state ends where single
+ * steps leave it, so that a graph of an even number of steps of a handle that has
+ * taken a step ends in the copy that it began with, and can be replayed.  From the
+ * first captured call on, calls and batch ticks of the handle outside the graph do
+ * so too: any even number of steps may stand between replays.  An odd number
+ * leaves the state in the copy that the graph does not read. */
 int lbem_step(lbem_t h, int64_t nsteps, const double* amp);
 
 /* E and B at the current time (3*n doubles each, component-major), recovered

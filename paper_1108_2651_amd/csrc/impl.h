@@ -222,6 +222,7 @@ struct lbem_s {
     bool ra_set;
     int64_t t;
     bool have_medium, have_fields;
+    bool graphed;            // lbem_step has been captured: a graph may hold the copies the state moves between
     Impl* impl;
     hipEvent_t sync_ev;      // set-up work on this handle's stream before a batch tick
     hipEvent_t tick_ev;      // end of the last batch tick that advanced this handle

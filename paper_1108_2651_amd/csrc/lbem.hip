@@ -1260,24 +1260,29 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     HIP_OK(follow_ticks(h));
     const int nf = fused_steps(h);
     const bool ext2 = h->D == 2 && has_bx(h);    // launches of four and two steps only
-    // Under stream capture the state ends in the buffer that single steps would
-    // leave it in, so that a graph of an even number of steps can be replayed:
-    // full launches by twos, the rest singly.
-    bool captured = false;
-    if (nf > 1 && nsteps > 1) {
+    // A graph holds the copies that its launches read and write.  So a captured
+    // call, and every later call on the handle (it may stand between two replays),
+    // leaves the state in the copy that single steps would leave it in: launches of
+    // several steps by twos, the rest singly.  The two P/J buffers of a pole, which
+    // only launches of several steps swap, come back as well.
+    if (!h->graphed) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
-        captured = st != hipStreamCaptureStatusNone;
+        h->graphed = st != hipStreamCaptureStatusNone;
     }
-    int64_t k = 0, twos = 0;
+    int64_t k = 0, twos = 0, each = 1;
     while (k < nsteps) {
         // 2D launches take any number of steps from two to nf (no three with extras)
         int64_t ns = std::min<int64_t>(nf, nsteps - k);
         if (ext2 && ns == 3) ns = 2;
-        if (captured) {
-            if (twos == 0 && h->layout == LAYOUT_PULL_PENDING && nsteps - k >= 2 * nf) twos = 2;
+        if (h->graphed) {
+            if (twos == 0 && h->layout == LAYOUT_PULL_PENDING) {
+                each = std::min<int64_t>(nf, (nsteps - k) / 2);
+                if (ext2 && each == 3) each = 2;
+                if (each > 1 && (h->D == 2 || each == nf)) twos = 2;
+            }
+            ns = twos > 0 ? each : 1;
             if (twos > 0) --twos;
-            else ns = 1;
         }
         if (ns > 1 && h->layout == LAYOUT_PULL_PENDING && (h->D == 2 || ns == nf)) {
             if (h->impl->step_fused(h, (amp && h->nsrc) ? amp + k : nullptr, (int)ns) != hipSuccess)
@@ -1699,6 +1704,9 @@ static MultiPlan plan_multi(const lbem_batch_s* b, int c, char* host, const lbem
     for (int q = 0; q < m; ++q) {
         const lbem_s* h = handles[idx[q]];
         if (class_of(h) != c) continue;
+        // a graph of the member's steps counts on the copy that single steps leave
+        // its state in (lbem_step)
+        if (h->graphed) return p;
         // a source needs its segments (a 3D handle below the solo kernel's size
         // rule has none)
         if (h->nsrc && !(D == 2 ? h->nmsrc > 0 : h->psrc_idx != nullptr)) return p;
