@@ -1265,17 +1265,25 @@ int lbem_step(lbem_t h, int64_t nsteps, const double* amp)
     // leaves the state in the copy that single steps would leave it in: launches of
     // several steps by twos, the rest singly.  The two P/J buffers of a pole, which
     // only launches of several steps swap, come back as well.
-    if (!h->graphed) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
-        h->graphed = st != hipStreamCaptureStatusNone;
-    }
-    int64_t k = 0, twos = 0, each = 1;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
+    const bool captured = st != hipStreamCaptureStatusNone;
+    h->graphed = h->graphed || captured;
+    // A captured odd number of steps of a plain format without extras, which has no
+    // such buffers, can be replayed too: an even number of launches, of even lengths.
+    const bool even = captured && nf > 1 && nsteps % 2 && h->prec <= LBEM_F32 && !has_bx(h) &&
+                       (h->D == 2 || (double)h->n >= FUSE3D_MIN);
+    int64_t k = 0, twos = 0, each = 1, left = 0;
     while (k < nsteps) {
         // 2D launches take any number of steps from two to nf (no three with extras)
         int64_t ns = std::min<int64_t>(nf, nsteps - k);
         if (ext2 && ns == 3) ns = 2;
-        if (h->graphed) {
+        if (even && h->layout == LAYOUT_PULL_PENDING) {
+            const int64_t to_go = nsteps - k;
+            if (left == 0) left = std::min<int64_t>(to_go, ((to_go + nf - 1) / nf + 1) / 2 * 2);
+            ns = (to_go + left - 1) / left;
+            --left;
+        } else if (h->graphed) {
             if (twos == 0 && h->layout == LAYOUT_PULL_PENDING) {
                 each = std::min<int64_t>(nf, (nsteps - k) / 2);
                 if (ext2 && each == 3) each = 2;

@@ -85,3 +85,24 @@ def test_even_calls_between_replays(dim, shape, prec, env, pole):
         batch.close()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("dim,shape,prec,n", [(2, (130, 40, 1), "f32", 5), (2, (130, 40, 1), "f32", 7),
+                                              (2, (60, 50, 1), "f64", 3), (3, (104, 100, 100), "f32", 3),
+                                              (3, (104, 100, 100), "f32", 7)])
+def test_odd_captures_of_plain_formats(dim, shape, prec, n):
+    """An odd number of steps, more than one, of FP32 and FP64 without extras replays
+    as well."""
+    import torch
+    st = torch.cuda.Stream()
+    a, b = handles(dim, shape, prec, {}, False, st)
+    g = capture(a, st, n)
+    for k in range(3):
+        announce(f"replay {dim}D {shape} {prec}: {n} steps, {k}")
+        replay(g, st)
+        b.step(n)
+        assert same(a, b), k
+        a.step(4)
+        b.step(4)
+    a.close()
+    b.close()
