@@ -988,17 +988,12 @@ __device__ __forceinline__ float dev_code_of(const Get& get, int i, int p)
     return sum;
 }
 
-// g0 of a moving population: half of Lambda_p + c_ia Bbar_b - c_ib Bbar_a,
-// formed from the halved moments.  Halving is exact, so this has the bits of
-// 0.5 * twice_eq_moving() (but for subnormal moments), and the six halved
-// moments serve all the populations of a cell.
+// g0 of a moving population: half of Lambda_p + c_ia Bbar_b - c_ib Bbar_a.  The
+// sum is halved, not the moments: halves of subnormal moments would round.
 template <int D>
 __device__ __forceinline__ float half_eq(int i, int p, const float (&Lam)[Lat<D>::P], const float (&Bb)[D])
 {
-    float hB[D];
-#pragma unroll
-    for (int e = 0; e < D; ++e) hB[e] = 0.5f * Bb[e];
-    return twice_eq_moving<D, float>(i, p, 0.5f * Lam[p], hB);
+    return 0.5f * twice_eq_moving<D, float>(i, p, Lam[p], Bb);
 }
 
 // Population (i,p) of one cell from its moments, codes and scale s: the
