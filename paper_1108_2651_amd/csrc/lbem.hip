@@ -190,8 +190,10 @@ static void make_pairf_geo(lbem_s* h)
     h->pair_f32 = fits && env_int("LBEM_PAIR3F", !odd && !asked) != 0;
 }
 
-// Strips and chunks of the 2D march for `waves` resident waves per SIMD.
-static void make_march_chunks(const lbem_s* h, int waves, MarchGeo& g, int& wpb)
+// Strips and chunks of the 2D march for `waves` resident waves per SIMD.  share:
+// what each further wave of a SIMD adds to a row of the march, as a part of what a
+// lone wave waits for; 0 keeps all waves resident.
+static void make_march_chunks(const lbem_s* h, int waves, double share, MarchGeo& g, int& wpb)
 {
     const int nx = (int)h->cfg.nx, ny = (int)h->cfg.ny;
     g.nx = nx; g.ny = ny; g.n = h->n;
@@ -206,9 +208,31 @@ static void make_march_chunks(const lbem_s* h, int waves, MarchGeo& g, int& wpb)
     const int64_t slots = 1024 * waves;
     const int64_t want = std::max<int64_t>(1, ((int64_t)g.strips * ny + slots - 1) / slots);  // rows if all fit
     const int64_t rounds = (want + 23) / 24;
-    const int64_t per = rounds * slots;
-    const int64_t chunks = std::max<int64_t>(1, per / g.strips);     // that fit these rounds
-    g.rows = (int)std::min<int64_t>(ny, std::max<int64_t>(2, (ny + chunks - 1) / chunks));
+    auto rows_of = [&](int64_t per) {
+        const int64_t chunks = std::max<int64_t>(1, per / g.strips);     // that fit these rounds
+        return (int)std::min<int64_t>(ny, std::max<int64_t>(2, (ny + chunks - 1) / chunks));
+    };
+    g.rows = rows_of(rounds * slots);
+    // Where one round suffices, fewer waves with more rows each recompute less:
+    // as many per SIMD as give the least rows marched, 8 of them beyond a chunk's
+    // own, times what a row takes.  A row of FP32 500^2 takes 0.30, 0.37 and 0.44 us
+    // with one, two and three waves on a SIMD, of FP64 0.30, 0.52 and 0.70.  Measured,
+    // us per step, all waves -> this: FP32 500^2 1.63 -> 1.51, 700^2 1.96 -> 1.88,
+    // 1000^2 2.99 -> 2.72, 1201x900 with a varying mu 4.15 -> 3.77; FP64 500^2 2.55
+    // -> 1.82, with mu 3.34 -> 2.30, 1000^2 5.1 -> 4.3; FP16-dev 500^2 3.10 -> 2.40.
+    if (rounds == 1 && share > 0.0) {
+        double best = 0.0;
+        for (int w = waves; w >= 1; --w) {
+            const int r = rows_of((int64_t)1024 * w);
+            if (r > 64 - 2 * MARCH_HX) break;
+            const int64_t nw = (int64_t)g.strips * ((ny + r - 1) / r);
+            const double cost = (r + 8) * (1.0 + share * (double)((nw + 1023) / 1024));
+            if (w == waves || cost < best) {
+                best = cost;
+                g.rows = r;
+            }
+        }
+    }
     g.nwork = g.strips * ((ny + g.rows - 1) / g.rows);
     // few waves: one per block, so that they spread over the CUs (96x64 3.6
     // against 4.0 us per launch)
@@ -258,9 +282,9 @@ static void make_fused_geo(lbem_s* h)
     // Waves resident per SIMD without extras, with walls or an absorber and with
     // a pole, by their registers (one / two cells per lane in FP32, FP64).
     const int w1 = h->prec == LBEM_F64 ? 2 : 4, w2 = h->prec == LBEM_F64 ? 1 : 3;
-    make_march_chunks(h, h->mcpl == 2 ? 2 : 4, h->mgeo, h->mwpb);
-    make_march_chunks(h, h->mcpl == 2 ? 2 : w1, h->mgeo_x[0], h->mwpb_x[0]);
-    make_march_chunks(h, h->mcpl == 2 ? 1 : w2, h->mgeo_x[1], h->mwpb_x[1]);
+    make_march_chunks(h, h->mcpl == 2 ? 2 : 4, h->prec == LBEM_F64 ? 1.5 : 0.4, h->mgeo, h->mwpb);
+    make_march_chunks(h, h->mcpl == 2 ? 2 : w1, 0.0, h->mgeo_x[0], h->mwpb_x[0]);
+    make_march_chunks(h, h->mcpl == 2 ? 1 : w2, 0.0, h->mgeo_x[1], h->mwpb_x[1]);
 }
 
 static void make_zmarch_geo(lbem_s* h)
