@@ -174,20 +174,35 @@ static void make_pairf_geo(lbem_s* h)
     const double share = (double)g.n / ((double)((g.nblocks + cus - 1) / cus) * cus * (g.lz + 2) * (PFX * PFY));
     h->ext_ns = fits && env_int("LBEM_FUSE3", share >= 0.25 ? 2 : 1) == 2 ? 2 : 1;
     if ((double)h->n < FUSE3D_MIN) h->fuse_ns = h->ext_ns;
-    // Without extras the column tiles of k_step_fused3d stay, from FUSE3D_MIN
-    // cells on, for up to 4e6 cells whose rows are several tiles and no whole
-    // 64-byte sectors (us per step, those / these: 90x150x150 57 / 63,
-    // 124x126x128 45 / 49, 150^3 91 / 98, though 140x120x110 58 / 54), and for up
-    // to 3e7 cells where every axis is whole 128s, so that those tiles and
-    // chunks are all full (128^3 46.1 / 47.2, 256^3 303.6 / 303.4, with a
-    // source 306 / 311).  Elsewhere these are faster: 112^3 27.4 / 23.7, 144^3
-    // 77 / 68, 160^3 97 / 88, 256x100x100 61 / 51, 256x256x60 83 / 76,
-    // 48x200x200 50 / 38, 250x190x171 212 / 172 (with a source 181), 320^3 622
-    // / 590, 512^3 2529 / 2422.
-    const bool odd = (double)h->n >= FUSE3D_MIN && ((g.tiles_x > 1 && g.nx % 16 != 0 && (double)h->n < 4.0e6) ||
-                                                    ((g.nx | g.ny | g.nz) % 128 == 0 && (double)h->n < 3.0e7));
+    // Without extras the column tiles of k_step_fused3d (smaller, two blocks per CU)
+    // stay, from FUSE3D_MIN cells on and for rows of several tiles, in four cases (us
+    // per step, column tiles / these):
+    // - within the Infinity Cache, where they need at most a block per CU, which then
+    //   runs alone: 1024x32x32 19.3 / 21.7, 256x64x64 20.0 / 20.9, 128x128x64 20.0 /
+    //   20.2 (not 192x64x96, 288 blocks, 26.9 / 20.9);
+    // beyond it
+    // - rows that are no whole 64-byte sectors and fill their tiles of 64 columns to
+    //   less than 60 on average (a tile holds a CU however few columns it has):
+    //   66x400x400 265 / 382, 102x189x224 116 / 127, 257^3 483 / 518, 330^3 871 / 947,
+    //   350^3 1049 / 1144, 200^3 199 / 211 (not 250x190x171 212 / 172, 188x200x200 183
+    //   / 158, 505x100x90 114 / 101; on the line 230^3 330 / 308, 348x135x168 186 / 203);
+    // - rows of 16 tiles and more, of which few fit the CUs at a time: 1010x60x60 89 /
+    //   99, 2000x60x40 99 / 105, 2048x64x64 161 / 167, 1024x64x64 86.7 / 85.8;
+    // - where all their blocks are resident at once and less of their work is idle:
+    //   128^3 46.0 / 46.8, 256x64x128 46.1 / 47.5, 124x126x128 45.5 / 48.9 (not
+    //   127x120x120 44.9 / 41.1).
+    // Elsewhere these are faster: 112^3 29.3 / 25.2, 144^3 75.7 / 67.7, 192^3 149 /
+    // 137, 224^3 255 / 216, 256^3 302.4 / 298.6, 312^3 705 / 600, 512^3 2529 / 2422.
+    const double state = 172.0 * (double)h->n;       // both copies and c_L^2
+    const double share_col = (double)g.n / ((double)((h->fgeo.nblocks + 2 * cus - 1) / (2 * cus)) * 2 * cus *
+                                            (h->f3_lz + 2) * (h->f3_tx * h->f3_ty));
+    bool col;
+    if (state <= 256.0 * (1 << 20)) col = h->fgeo.nblocks <= cus;
+    else col = (g.nx % 16 != 0 && g.nx < 60 * g.tiles_x) || g.tiles_x >= 16 ||
+               (h->fgeo.nblocks <= 2 * cus && share < share_col);
+    col = col && g.tiles_x > 1 && (double)h->n >= FUSE3D_MIN;
     const bool asked = std::getenv("LBEM_FUSE3_TX") != nullptr || std::getenv("LBEM_FUSE3_TY") != nullptr;
-    h->pair_f32 = fits && env_int("LBEM_PAIR3F", !odd && !asked) != 0;
+    h->pair_f32 = fits && env_int("LBEM_PAIR3F", !col && !asked) != 0;
 }
 
 // Strips and chunks of the 2D march for `waves` resident waves per SIMD.  share:
