@@ -1118,8 +1118,9 @@ int lbem_set_dispersion(lbem_t h, const double* wp2, const double* w02, const do
             h->ade = h->pol = nullptr;
             return LBEM_ENOMEM;
         }
-        // two-step launches need a second copy; without it the steps stay single
-        if (h->ext_ns > 1 && hipMalloc(&h->pol2, pb) != hipSuccess) {
+        // launches of several steps (in 3D: not with walls) need a second copy;
+        // without it the steps stay single
+        if (h->ext_ns > 1 && (h->D == 2 || !ext_of(h).walls()) && hipMalloc(&h->pol2, pb) != hipSuccess) {
             h->pol2 = nullptr;
             (void)hipGetLastError();
         }
