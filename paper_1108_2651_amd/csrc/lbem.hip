@@ -648,36 +648,41 @@ static void free_source(lbem_s* h)
 // Per-block source entries of the fused 3D tiling: every (plane offset,
 // frame cell) of the block's z range z0-1 .. z0+lz (periodic images included)
 // that carries a current; entry.x = plane offset * frame cells + frame cell.
-static int build_fused3_source(lbem_s* h, const std::vector<double>& dense, int pp)
+static int build_fused3_source(lbem_s* h, const std::vector<std::pair<int64_t, double>>& cells, int pp)
 {
     const Geo& g = h->fgeo;
     const int TX = h->f3_tx, TY = h->f3_ty, LZ = h->f3_lz;
     const int W = TX + 2, HH = TY + 2, FC = W * HH;
+    // per coordinate of an axis the tiles whose frame holds it, and where
+    auto frames = [](int n, int step, int count) {
+        std::vector<std::vector<std::pair<int, int>>> of(n);
+        for (int t = 0; t < count; ++t)
+            for (int j = 0; j < step + 2; ++j) of[((t * step - 1 + j) % n + n) % n].push_back({t, j});
+        return of;
+    };
+    const auto fx = frames(g.nx, TX, g.tiles_x), fy = frames(g.ny, TY, g.tiles_y),
+               fz = frames(g.nz, LZ, (g.nz + LZ - 1) / LZ);
+    struct Item { int b, local; double v; };
+    std::vector<Item> items;
+    for (auto& e : cells) {
+        if (e.second == 0.0) continue;
+        const int64_t r = e.first / g.nx;          // row index y + ny z
+        for (auto& z : fz[r / g.ny])
+            for (auto& y : fy[r % g.ny])
+                for (auto& x : fx[e.first % g.nx])
+                    items.push_back({(z.first * g.tiles_y + y.first) * g.tiles_x + x.first,
+                                     z.second * FC + y.second * W + x.second, e.second});
+    }
+    std::sort(items.begin(), items.end(),
+              [](const Item& a, const Item& b2) { return a.b != b2.b ? a.b < b2.b : a.local < b2.local; });
     std::vector<int> off(g.nblocks + 1, 0);
-    std::vector<int2> ent;
-    std::vector<double> val;
-    for (int b = 0; b < g.nblocks; ++b) {
-        const int tx = b % g.tiles_x, r = b / g.tiles_x;
-        const int ty = r % g.tiles_y, zc = r / g.tiles_y;
-        const int x0 = tx * TX, y0 = ty * TY, z0 = zc * LZ;
-        for (int po = 0; po < LZ + 2; ++po) {
-            int gz = (z0 - 1 + po) % g.nz;
-            if (gz < 0) gz += g.nz;
-            for (int hy = 0; hy < HH; ++hy) {
-                int gy = (y0 - 1 + hy) % g.ny;
-                if (gy < 0) gy += g.ny;
-                for (int hx = 0; hx < W; ++hx) {
-                    int gx = (x0 - 1 + hx) % g.nx;
-                    if (gx < 0) gx += g.nx;
-                    const double v = dense[(size_t)gx + (size_t)g.nx * ((size_t)gy + (size_t)g.ny * gz)];
-                    if (v != 0.0) {
-                        ent.push_back(make_int2(po * FC + hy * W + hx, pp));
-                        val.push_back(v);
-                    }
-                }
-            }
-        }
-        off[b + 1] = (int)ent.size();
+    for (auto& it : items) off[it.b + 1]++;
+    for (int b = 0; b < g.nblocks; ++b) off[b + 1] += off[b];
+    std::vector<int2> ent(items.size());
+    std::vector<double> val(items.size());
+    for (size_t k = 0; k < items.size(); ++k) {
+        ent[k] = make_int2(items[k].local, pp);
+        val[k] = items[k].v;
     }
     const size_t ms = ent.size(), tv = h->prec == LBEM_F64 ? 8 : 4;
     if (hipMalloc((void**)&h->fsrc_off, off.size() * sizeof(int)) != hipSuccess ||
@@ -1278,16 +1283,10 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
     if (fused_format(h) && h->fuse_ns > 1 && !(pair32 && h->pair_f32)) {
-        int rc;
-        if (D == 2 || is_dev(h->prec)) {
-            std::vector<std::pair<int64_t, double>> cv(merged.size());
-            for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
-            rc = D == 2 ? build_march_source(h, cv) : build_pair_source(h, cv, pp);
-        } else {
-            std::vector<double> dense((size_t)n, 0.0);
-            for (size_t k = 0; k < merged.size(); ++k) dense[(size_t)merged[k].first] = src_value[k];
-            rc = build_fused3_source(h, dense, pp);
-        }
+        std::vector<std::pair<int64_t, double>> cv(merged.size());
+        for (size_t k = 0; k < merged.size(); ++k) cv[k] = {merged[k].first, src_value[k]};
+        const int rc = D == 2 ? build_march_source(h, cv)
+                              : (is_dev(h->prec) ? build_pair_source(h, cv, pp) : build_fused3_source(h, cv, pp));
         if (rc != LBEM_OK) { free_source(h); return rc; }
     }
     return LBEM_OK;
