@@ -188,18 +188,18 @@ static void make_pairf_geo(lbem_s* h)
     //   / 158, 505x100x90 114 / 101; on the line 230^3 330 / 308, 348x135x168 186 / 203);
     // - rows of 16 tiles and more, of which few fit the CUs at a time: 1010x60x60 89 /
     //   99, 2000x60x40 99 / 105, 2048x64x64 161 / 167, 1024x64x64 86.7 / 85.8;
-    // - where all their blocks are resident at once and less of their work is idle:
-    //   128^3 46.0 / 46.8, 256x64x128 46.1 / 47.5, 124x126x128 45.5 / 48.9 (not
-    //   127x120x120 44.9 / 41.1).
+    // - where clearly less of their work is idle: 128^3 46.0 / 46.8, 256x64x128 46.1 /
+    //   47.5, 124x126x128 45.5 / 48.9, 256^3 302.4 / 298.6 but with a source 306.1 /
+    //   308.0 (not 127x120x120 44.9 / 41.1, 250^3 388 / 345).
     // Elsewhere these are faster: 112^3 29.3 / 25.2, 144^3 75.7 / 67.7, 192^3 149 /
-    // 137, 224^3 255 / 216, 256^3 302.4 / 298.6, 312^3 705 / 600, 512^3 2529 / 2422.
+    // 137, 224^3 255 / 216, 312^3 705 / 600, 512^3 2529 / 2422.
     const double state = 172.0 * (double)h->n;       // both copies and c_L^2
     const double share_col = (double)g.n / ((double)((h->fgeo.nblocks + 2 * cus - 1) / (2 * cus)) * 2 * cus *
                                             (h->f3_lz + 2) * (h->f3_tx * h->f3_ty));
     bool col;
     if (state <= 256.0 * (1 << 20)) col = h->fgeo.nblocks <= cus;
     else col = (g.nx % 16 != 0 && g.nx < 60 * g.tiles_x) || g.tiles_x >= 16 ||
-               (h->fgeo.nblocks <= 2 * cus && share < share_col);
+               share < 0.96 * share_col;
     col = col && g.tiles_x > 1 && (double)h->n >= FUSE3D_MIN;
     const bool asked = std::getenv("LBEM_FUSE3_TX") != nullptr || std::getenv("LBEM_FUSE3_TY") != nullptr;
     h->pair_f32 = fits && env_int("LBEM_PAIR3F", !col && !asked) != 0;
