@@ -49,7 +49,9 @@ __global__ __launch_bounds__(1024, 4) void k_batch_pair3d(const BatchHdr* __rest
     if (G.nsteps - 1 < 2 * (j + 1)) return;
     const int s = (G.cur0 + 1 + j) & 1;
     const PairGeo g = G.pgeo;
-    const int t = b - G.multi_base, tx = t % g.tiles_x, r = t / g.tiles_x;
+    // a member's tiles are dealt to the XCDs as the solo launch deals them (its first
+    // block may run on any of the 8)
+    const int t = remap_block(b - G.multi_base, g.nblocks, g.xcd), tx = t % g.tiles_x, r = t / g.tiles_x;
     const int y0 = (r % g.tiles_y) * g.sy, z0 = (r / g.tiles_y) * g.lz;
     const PairSrc ps{nullptr, gmem<const int>(G.psrc_idx), gmem<const float>(G.psrc_val), G.psrc_pair};
     AmpPack<float, 2> a;
