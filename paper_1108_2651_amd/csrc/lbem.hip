@@ -1793,10 +1793,14 @@ static MultiPlan plan_multi(const lbem_batch_s* b, int c, char* host, const lbem
             const int64_t cost = (nb + cus - 1) / cus * (z + 4);
             if (best < 0 || cost < best) { best = cost; lz = z; }
         }
-        // the share of the work that is on stored cells, as for a single lattice
+        // the share of the work that is on stored cells, as for a single lattice.  us
+        // per tick of 50 steps, single steps / pairs (share), FP16 ghost: 48^3 + 32^3 +
+        // 48^3 + 64^3 (0.28) 879 / 936, 20 + 48 + 96 + 20 (0.46) 1456 / 1126, 96^3 (0.48)
+        // 1253 / 963, 128^3 (0.49) 2500 / 1983; FP16-dev 128^3 3799 / 2788, 96^3 1324 /
+        // 1129.
         const bool ghost = prec == LBEM_F16GHOST || prec == LBEM_BF16GHOST;
         const double share = (double)cells / ((double)best * cus * (PRX * PRY));
-        if (b->multi < 2 && share < (ghost ? 0.28 : 0.36) + (lines ? 0.09 : 0.0)) return MultiPlan{};
+        if (b->multi < 2 && share < (ghost ? 0.30 : 0.36) + (lines ? 0.09 : 0.0)) return MultiPlan{};
         for (int k = 0; k < cnt; ++k) {
             PairGeo& g = tab[k].pgeo;
             g = mem[k]->pgeo;
