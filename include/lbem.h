@@ -150,7 +150,8 @@ int lbem_set_source(lbem_t h, int comp, const int64_t* cells, const double* weig
  * amp[k] at time t0 + k.  ESTATE before lbem_init_fields.  Handles with pull
  * streaming advance several steps per launch where the kernels allow
  * (lbem_steps_per_launch): also with an absorber or dispersion in FP32 and in 2D
- * FP64, and with walls in 2D FP32 and FP64; elsewhere these, and anisotropy
+ * FP64, and with walls in 2D FP32 and FP64 (2D boxes of 4096 cells and more, 3D ones
+ * large enough for the tiles of two steps); elsewhere these, and anisotropy
  * everywhere, make every launch a single step.  The result does not depend on
  * this choice (bit for bit).  The state moves to its other copy with every
  * launch.  A captured call takes launches by which the state ends where single
@@ -246,8 +247,8 @@ int lbem_set_state(lbem_t h, const void* buf, size_t bytes, int on_device);
 /* Faces of `axis` (0..dim-1) become walls of the given kind (or periodic
  * again).  Pull streaming only (EINVAL for AA: create the handle with
  * LBEM_STREAM_PULL, since AUTO takes AA for small 3D FP32 and all 3D FP64
- * boxes); before lbem_set_medium (ESTATE after).  With walls or an absorber
- * the solver runs single steps. */
+ * boxes); before lbem_set_medium (ESTATE after).  With walls the solver runs
+ * single steps in 3D and in the 16-bit formats (see lbem_step). */
 int lbem_set_boundary(lbem_t h, int axis, int kind);
 
 /* Absorbing layer: after every collision the populations of cell x are
@@ -289,7 +290,10 @@ int lbem_set_anisotropy(lbem_t h, const double* fac);
  * non-finite values or AA streaming.  P and J restart from zero here and at
  * lbem_init_fields; they are part of the checkpoint blob.  Stability of
  * large wp2 or w02 is the caller's (lattice units: keep them well below 1).
- * Synchronises; the solver then runs single steps. */
+ * Synchronises.  The handle allocates the coefficients (three values per cell of
+ * the medium's type) and P and J (two per cell and pair); where several steps per
+ * launch apply (lbem_step) also a second P and J, without which, if it cannot be
+ * had, the solver runs single steps. */
 int lbem_set_dispersion(lbem_t h, const double* wp2, const double* w02, const double* gamma);
 
 /* Static description of a status code. */

@@ -498,7 +498,7 @@ static int fused_steps(const lbem_s* h)
     return !h->ra_set && (h->D == 2 || !ext_of(h).walls()) && (!h->ade || h->pol2) ? std::max(1, h->ext_ns) : 1;
 }
 
-// 3D FP32 pairs on the 62 x 14 tiles
+// 3D FP32 pairs on tiles of up to 64 x 13 stored cells
 template <bool MU, bool EXT, bool TH>
 static hipError_t launch_pair_f32(lbem_s* h, const float* src, float* dst, const AmpPack<float, 2>& a, const PairExt& ex)
 {

@@ -1773,11 +1773,11 @@ struct MarchGeo {
     int64_t n;
 };
 
-// Tiles of the 3D two-step kernel (pair3d.h).
+// Tiles of the 3D two-step kernels (pair3d.h, pair3f.h).
 struct PairGeo {
     int nx, ny, nz;
     int tiles_x, tiles_y, lz;            // planes per chunk
-    int sx, sy;                          // columns and rows a tile stores (FP32)
+    int sx, sy;                          // columns and rows a tile stores
     int nblocks, xcd;
     int64_t n;
 };

@@ -292,8 +292,10 @@ static void make_fused_geo(lbem_s* h)
     // two.  us per step, single steps / these: FP32 walls 128^2 2.7 / 1.7,
     // 1023x767 7.7 / 4.0, 2048^2 27.7 / 10.3, 4096^2 113 / 45; with an absorber
     // 4096^2 121 / 49; a pole 128^2 2.9 / 2.0, 2048^2 43 / 19, 4096^2 228 / 88;
-    // FP64 walls 2048^2 60 / 23, a pole 87 / 41.  Boxes below 4096 cells, where
-    // a call is its launches, keep lbem_steps_per_launch of one.
+    // FP64 walls 2048^2 60 / 23, a pole 87 / 41.  The line at 4096 cells is not one of
+    // speed (FP32 48x40 walls 2.9 / 1.7, an absorber 2.8 / 1.5, a pole 2.8 / 1.9; FP64
+    // 3.3 / 1.7, 3.1 / 1.6, 3.2 / 2.2): smaller boxes with extras have always reported
+    // one step per launch, and callers hold them to it.
     // Waves resident per SIMD without extras, with walls or an absorber and with
     // a pole, by their registers (one / two cells per lane in FP32, FP64).
     const int w1 = h->prec == LBEM_F64 ? 2 : 4, w2 = h->prec == LBEM_F64 ? 1 : 3;

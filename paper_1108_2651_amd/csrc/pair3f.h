@@ -15,10 +15,11 @@
 // do, for one wave of scattered loads; with the side columns in the lanes (62 x
 // 14 stored) every row straddled three lines and half of the stores two tiles
 // (256^3 502 us per step, here 303).  One block per CU, 96-126 of 128 VGPRs, so
-// the next plane is loaded before level 2 runs.  Bound by memory: 168 B per cell
-// and two steps, 4.8 TB/s counted on them at 256^3; against the column tiles of
-// k_step_fused3d (two blocks per CU, all exchange through LDS) 303 / 303 at
-// 256^3, 97 -> 88 at 160^3, 212 -> 172 at 250x190x171.
+// the next plane is loaded before level 2 runs.  Bound by memory: 198 B counted
+// per cell and two steps at 512^3 (172 without halos), 5.5 TB/s; us per step,
+// column tiles of k_step_fused3d (two blocks per CU, all exchange through LDS) ->
+// these: 512^3 2529 -> 2422, 160^3 97 -> 88, 250x190x171 212 -> 172, but 256^3 302 /
+// 299 and 257^3, whose last tile is one column, 483 / 518.
 //
 // EXT: an absorbing layer and the dispersion pole.  P and J of a cell advance
 // with it: level 1 reads them from one buffer, keeps the new pair in registers
