@@ -378,6 +378,11 @@ struct SrcArgs {
     T amp;
 };
 
+// S of a cell in a segment of source values: 0 where the cell carries none, also
+// for an amplitude that is not finite
+template <typename T>
+__device__ __forceinline__ T source_term(T val, T amp) { return val != T(0) ? val * amp : T(0); }
+
 template <int P, int VEC, typename T>
 __device__ __forceinline__ bool stage_source(const SrcArgs<T>& s, int b, T* lds)
 {

@@ -376,7 +376,7 @@ __device__ __forceinline__ void march2d_item(const IO& io, const typename IO::T*
                 for (int c = 0; c < CPL; ++c) {
                     T rho[1], K[2], Sp[1];
                     moments<2, T>(f[c], rho, K);
-                    Sp[0] = SRC ? sv[SRC ? q : 0][c] * amps.a[s - 1] : T(0);
+                    Sp[0] = SRC ? source_term(sv[SRC ? q : 0][c], amps.a[s - 1]) : T(0);
                     if constexpr (MU) {
                         const T d2[2] = {dl[MU ? q : 0][0][c], dl[MU ? q : 0][1][c]};
                         add_mu_source<2, T>(K, cl[q][c], d2, Sp);

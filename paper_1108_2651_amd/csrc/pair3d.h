@@ -198,13 +198,13 @@ __device__ __forceinline__ void pair_march(const float* Min, const H* Din, float
         if (it >= 2 && !edge) {
             float M[NM];
             H code[NC];
-            update(L0, ly[br][0], mz0, cl1, wc1, rw1, sv1 * amps.a[0], z0 - 3 + it, M, code);
+            update(L0, ly[br][0], mz0, cl1, wc1, rw1, SRC ? source_term(sv1, amps.a[0]) : 0.f, z0 - 3 + it, M, code);
             spread(M, code, wc1, ly[bw][1], inner, N1, mz1);
         }
         if (it >= 4 && inner) {
             float M[NM];
             H code[NC];
-            update(L1, ly[br][1], mz1, cl2, wc2, rw2, sv2 * amps.a[1], z0 - 4 + it, M, code);
+            update(L1, ly[br][1], mz1, cl2, wc2, rw2, SRC ? source_term(sv2, amps.a[1]) : 0.f, z0 - 4 + it, M, code);
             const int64_t o = (int64_t)(z0 - 4 + it) * nxy + rowo;
             if (keep) {
                 unsigned col = col0;

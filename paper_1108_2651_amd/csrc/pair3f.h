@@ -171,7 +171,7 @@ __device__ __forceinline__ void pair_march_f(const float* src, float* dst, const
         for (int p = 0; p < P; ++p) { p0[p] = po[p]; j0[p] = jo[p]; }
         gz = gz + 1 == g.nz ? 0 : gz + 1;
         if (live) {
-            update(f, cl0, sv0 * amps.a[0], z0 - 1 + it, ca0, p0, j0, kp0, out);
+            update(f, cl0, SRC ? source_term(sv0, amps.a[0]) : 0.f, z0 - 1 + it, ca0, p0, j0, kp0, out);
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 if (sides) {
@@ -196,7 +196,7 @@ __device__ __forceinline__ void pair_march_f(const float* src, float* dst, const
                 f2[5][p] = ly[br][P + p][tid + 64];
                 f2[6][p] = out[6][p];
             }
-            update(f2, cl1, sv1 * amps.a[1], z0 - 2 + it, ca1, p1, j1, kp1, o2);
+            update(f2, cl1, SRC ? source_term(sv1, amps.a[1]) : 0.f, z0 - 2 + it, ca1, p1, j1, kp1, o2);
             const int64_t o = (int64_t)(z0 - 2 + it) * nxy;
             if (keep) {
                 unsigned c = c0;
