@@ -21,9 +21,9 @@
 // of 128 VGPRs); a narrower or lower tile recomputes and re-reads more.  What
 // bounds it: L1 -> L2 requests (0.12 per cycle and CU, the rate of every 3D
 // kernel here) and bytes: counted traffic of 147 B per cell and two steps at
-// 512^3, 4.61 TB/s, the rate of a large copy, against 254 B of two single
+// 512^3, 4.62 TB/s, the rate of a large copy, against 254 B of two single
 // steps.  With every plane the same (no traffic beyond L2) a launch there takes
-// 2.67 of its 4.28 ms.  Stores are plain: the partial lines at tile edges
+// 2.67 of its 4.27 ms.  Stores are plain: the partial lines at tile edges
 // merge in L2 (streaming stores ran 5.7 against 4.4 ms, on full tiles).  Tiles are dealt to
 // the XCDs in runs of one row of tiles, which share their x-halo lines (512^3,
 // us per launch, runs of 0 / 1 / 3 / 9 tiles: 5350 / 5340 / 4810 / 4360).
